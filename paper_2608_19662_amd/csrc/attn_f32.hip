@@ -1,15 +1,39 @@
-// fp32 attention for the reference-precision path (encode and conversation
-// attend).  One wave per (query row, head): the lanes split head_dim, each
-// key's logit is a wave reduction, and the softmax is accumulated online in
-// fp32 with exp2.  It exists to run the method exactly at fp32 input
-// precision (no bf16 rounding anywhere); the bf16 MFMA kernels are the
-// throughput path.
+// fp32 attention (encode, conversation prefill and decode) on the fp32 matrix
+// instructions of gfx950.  Every product and sum stays in fp32: it runs the
+// method at fp32 input precision, with no bf16 rounding anywhere.
 //
 // Visibility follows the same definitions as the bf16 kernels: encode rows
 // see the shared prefix and their own resource causally (ReCache Sec. 3,
 // "Resource-Wise Attention"); conversation rows see the kept rows of their routed resources
 // in request order and then the context causally, bottom-right aligned
 // (Fig. 2, final mask).
+//
+// Work decomposition.  The query rows of a unit and KV group are flattened to
+// columns j = row * ratio + head, and a block owns 32 of them: few queries
+// still fill the matrix tile when they have several heads, and a causal block
+// of 32 columns spans only 32 / ratio rows.  Its four waves take the 32-key
+// tiles of the key stream in turn, each with its own softmax state, merged in
+// LDS at the end: fp32 calls are small (short streams, few columns), so the
+// keys are split to have enough waves, and always four ways, so that a
+// resource's results do not depend on what is packed beside it.  Per tile
+//     S^T = K Q^T      (32x32x2 fp32 MFMA; A = K straight from memory in
+//                       VGPRs, B = Q^T in VGPRs)
+//     O^T += V^T P^T   (A = V rows from LDS, B = P^T as it stands in the S^T
+//                       accumulators)
+// so that a lane owns one column, and half of its keys and dims.  The order
+// of the MFMA's inner index is free: half h of the lanes holds dims 8 j + 4 h
+// + [0, 4) of Q and K (one 16-byte load each), and the keys that the S^T
+// accumulators leave in half h of P.
+//
+// Bound: the fp32 matrix rate (a wave tile is 128 MFMAs of 64 cycles at
+// head_dim 128; its 32 KB of K and V ask the L2 for 16 B/clk per CU).  The K
+// loads of the next tile are issued behind this tile's S products and the V
+// copies of a tile before them, so both have a product's time to land.
+// Measured at 32 / 8 heads, head_dim 128: six resources of 100 to 500 tokens
+// encode in 140 us (one wave per row and head, a shuffle reduction per key:
+// 965 us), two requests of 150 to 250 queries over them attend in 73 us (669).
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -17,127 +41,368 @@ namespace rc {
 
 namespace {
 
-struct OnlineSoftmax {
-    float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-    __device__ __forceinline__ void add(float s2, float v0, float v1) {
-        const float mn = fmaxf(m, s2);
-        const float alpha = exp2f(m - mn);
-        const float p = exp2f(s2 - mn);
-        l = l * alpha + p;
-        o0 = o0 * alpha + p * v0;
-        o1 = o1 * alpha + p * v1;
-        m = mn;
-    }
+constexpr int kThreads = 256;
+constexpr int kWaves = 4;
+constexpr int kCols = 32;     // columns (row, head) per block
+constexpr int kKeys = 32;     // keys per wave tile
+constexpr int kMaxSeg = 1024; // route segments per pass over the segment table
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+template <int HD>
+struct F32Smem {
+    int seg_start[kMaxSeg + 1];
+    int seg_row[kMaxSeg];
+    int scan[kWaves];
+    float ml[kWaves][kCols][2];
+    // per wave: the V tile [32 keys][HD]; before the loop the cos / sin table,
+    // after it the wave's O [32 columns][HD]
+    alignas(16) float v[kWaves][kKeys * HD];
 };
 
-template <bool ENCODE>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const AttnF32Args a) {
-    const int lane = threadIdx.x & 63;
-    const long w = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int head = (int)(w % a.n_q_heads);
-    const long rest = w / a.n_q_heads;
-    const int unit = (int)(rest % a.n_units);
-    const int row = (int)(rest / a.n_units);
-    if (row >= a.max_rows) return;
-    const int g = head / a.ratio;
-    const int d = a.head_dim;
-    const bool two = d == 128;  // lanes hold elements lane and lane + 64
+template <int HD, bool ENCODE>
+__global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args a) {
+    constexpr int NJ = HD / 8;    // 8-dim steps of S^T (four MFMAs each)
+    constexpr int NDB = HD / 32;  // 32-dim blocks of O^T
+    constexpr int LPR = HD / 4;   // lanes per row of a V copy (16 bytes each)
+    constexpr int NVC = kKeys * HD / 256;  // 1 KB copies per V tile
+    __shared__ F32Smem<HD> sm;
 
-    int q_row0, q_len;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int R = a.ratio;
+
+    // block -> (unit, column block [longest first], group)
+    int bid = blockIdx.x;
+    const int g = bid % a.n_kv_heads;
+    bid /= a.n_kv_heads;
+    const int cb = a.n_cb - 1 - bid % a.n_cb;
+    const int unit = bid / a.n_cb;
+
+    int q_row0, q_len, c0, tc;
     if constexpr (ENCODE) {
         q_row0 = a.cu_len[unit];
         q_len = a.cu_len[unit + 1] - q_row0;
+        c0 = q_row0;
+        tc = q_len;
     } else {
         q_row0 = a.cu_q[unit];
         q_len = a.cu_q[unit + 1] - q_row0;
+        c0 = a.cu_ctx[unit];
+        tc = a.cu_ctx[unit + 1] - c0;
     }
-    if (row == a.max_rows - 1 && q_len > a.max_rows) {
+    if (cb == a.n_cb - 1 && q_len > a.max_rows) {
         // rows past the grid's max_rows: NaN, so that a caller's size error
         // shows in the outputs instead of leaving them unwritten
-        for (int r = a.max_rows; r < q_len && (long)q_row0 + r < a.lse_rows; ++r) {
-            float* op = a.out + ((size_t)(q_row0 + r) * a.n_q_heads + head) * a.head_dim;
-            op[lane] = __builtin_nanf("");
-            if (a.head_dim == 128) op[lane + 64] = __builtin_nanf("");
-            if (a.lse && lane == 0) a.lse[(size_t)head * a.lse_rows + q_row0 + r] = __builtin_nanf("");
-        }
+        for (int r = a.max_rows; r < q_len && (long)q_row0 + r < a.lse_rows; ++r)
+            for (int i = tid; i < R * HD; i += kThreads) {
+                const int h = g * R + i / HD;
+                a.out[((size_t)(q_row0 + r) * a.n_q_heads + h) * HD + i % HD] = __builtin_nanf("");
+                if (i % HD == 0 && a.lse) a.lse[(size_t)h * a.lse_rows + q_row0 + r] = __builtin_nanf("");
+            }
     }
-    if (row >= q_len || q_row0 + row >= a.lse_rows) return;
+    const int rows = min(q_len, a.max_rows);
+    const int j0 = cb * kCols, n_cols = rows * R;  // (rows <= lse_rows: n_cols indexes LSE)
+    if (j0 >= n_cols) return;
+    const int used = min(kCols, n_cols - j0);   // columns of this block
+    const int my_j = j0 + min(l32, used - 1);   // spare lanes repeat the last column
+    const int my_row = my_j / R, my_head = my_j % R;
+    const int first_row = j0 / R, last_row = (j0 + used - 1) / R;
+    const long max_q = a.lse_rows - 1;  // rows outside [0, lse_rows) of q / out are never touched
 
-    const float* qp = a.q + ((size_t)(q_row0 + row) * a.n_q_heads + head) * d;
-    float q0 = qp[lane];
-    float q1 = two ? qp[lane + 64] : 0.f;
+    // ---- Q^T (B operand): dims 8 j + 4 half + [0, 4) of this lane's column
+    f32x4 qf[NJ];
+    {
+        const long row = max(0L, min((long)q_row0 + my_row, max_q));
+        const float* qp = a.q + ((size_t)row * a.n_q_heads + g * R + my_head) * HD + half * 4;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) qf[j] = *reinterpret_cast<const f32x4*>(qp + j * 8);
+    }
     if constexpr (ENCODE) {
-        const int pos = (a.pos_base ? a.pos_base[unit] : 0) + row;
-        float s, c;
-        if (two) {
-            // pair (lane, lane + 64), frequency lane
-            sincos_rev(rope_revolutions(pos, a.rope.rev[lane]), &s, &c);
-            // the rounding of the key rotation, written out
-            const float y0 = fmaf(q0, c, -(q1 * s)), y1 = fmaf(q1, c, q0 * s);
-            q0 = y0;
-            q1 = y1;
-        } else {
-            // pair (lane, lane + 32), frequency lane % 32
-            sincos_rev(rope_revolutions(pos, a.rope.rev[lane & 31]), &s, &c);
-            const float partner = __shfl_xor(q0, 32);
-            q0 = (lane < 32) ? fmaf(q0, c, -(partner * s)) : fmaf(q0, c, partner * s);
+        // RoPE at the resource-local position: cos / sin of the block's rows
+        // once per (row, frequency) into LDS; the pairs (f, f + HD / 2) are
+        // (j, j + NJ / 2) in this lane
+        constexpr int HALF = HD / 2;
+        float2* tab = reinterpret_cast<float2*>(&sm.v[0][0]);
+        const int pos0 = a.pos_base ? a.pos_base[unit] : 0;
+        const int n = (last_row - first_row + 1) * HALF;
+        for (int i = tid; i < n; i += kThreads) {
+            float s, c;
+            sincos_rev(rope_revolutions(pos0 + first_row + i / HALF, a.rope.rev[i % HALF]), &s, &c);
+            tab[i] = make_float2(c, s);
         }
+        __syncthreads();
+        const float2* t = tab + (my_row - first_row) * HALF + half * 4;
+#pragma unroll
+        for (int j = 0; j < NJ / 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float2 k = t[j * 8 + e];
+                const float x1 = qf[j][e], x2 = qf[j + NJ / 2][e];
+                // the rounding of the key rotation, written out
+                qf[j][e] = fmaf(x1, k.x, -(x2 * k.y));
+                qf[j + NJ / 2][e] = fmaf(x2, k.x, x1 * k.y);
+            }
+        __syncthreads();  // the table's place takes V tiles next
     }
     const float sc = a.scale * 1.44269504088896340736f;
 
-    OnlineSoftmax acc;
-    auto visit = [&](const float* kr, const float* vr) {
-        float part = q0 * kr[lane] + (two ? q1 * kr[lane + 64] : 0.f);
-        const float s2 = wave_sum(part) * sc;
-        acc.add(s2, vr[lane], two ? vr[lane + 64] : 0.f);
-    };
+    float m = -INFINITY, l = 0.f;  // this wave's reference max and this lane's part of the sum
+    f32x16 oacc[NDB];              // O^T: dims db*32 + 8 (r / 4) + 4 half + r % 4 of the column
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) oacc[db] = f32x16{};
 
+    // ---- the key stream: route segments (at most kMaxSeg per pass), the
+    // last pass followed by the causal rows
+    int n_seg, r0 = 0;
     if constexpr (ENCODE) {
-        // the shared prefix, fully visible, then the resource's own rows
-        const float* pk = a.k + (size_t)g * a.k_gstride * d;
-        const float* pv = a.v + (size_t)g * a.k_gstride * d;
-        for (int u = 0; u < a.p_len; ++u) visit(pk + (size_t)u * d, pv + (size_t)u * d);
-        const float* kb = a.ck + ((size_t)g * a.c_rows + q_row0) * d;
-        const float* vb = a.cv + ((size_t)g * a.c_rows + q_row0) * d;
-        for (int u = 0; u <= row; ++u) visit(kb + (size_t)u * d, vb + (size_t)u * d);
+        n_seg = a.p_len > 0 ? 1 : 0;
     } else {
         const size_t e = ((size_t)unit * a.n_layers + a.layer) * a.n_kv_heads + g;
-        const float* kb = a.k + (size_t)g * a.k_gstride * d;
-        const float* vb = a.v + (size_t)g * a.k_gstride * d;
-        for (int s = a.route_off[e]; s < a.route_off[e + 1]; ++s) {
-            const int r = a.route_res[s];
-            const int r_beg = a.res_off ? a.res_off[(size_t)r * a.n_kv_heads + g] : a.cu_kept[r];
-            const int r_end = min(r_beg + (a.cu_kept[r + 1] - a.cu_kept[r]), (int)a.k_rows);
-            for (int u = r_beg; u < r_end; ++u) visit(kb + (size_t)u * d, vb + (size_t)u * d);
+        r0 = a.route_off[e];
+        n_seg = a.route_off[e + 1] - r0;
+    }
+    const int off = tc - q_len;  // the row's last visible causal row is off + row
+    const int c_max = (int)min((long)a.c_rows - 1 - c0, (long)tc - 1);
+    const int my_last = min(off + my_row, c_max), block_last = min(off + last_row, c_max);
+    const int block_first = min(off + first_row, c_max);
+    float* vbuf = sm.v[wave];
+
+    for (int seg0 = 0;; seg0 += kMaxSeg) {
+        const bool last_pass = seg0 + kMaxSeg >= n_seg;
+        const int ns = max(0, min(kMaxSeg, n_seg - seg0));
+        int s_vis;
+        if constexpr (ENCODE) {
+            s_vis = a.p_len;
+            if (tid == 0) sm.seg_start[0] = 0, sm.seg_start[1] = s_vis, sm.seg_row[0] = 0;
+        } else {
+            if (seg0 > 0) __syncthreads();  // every wave is done with the previous pass's table
+            constexpr int SPT = kMaxSeg / kThreads;
+            int lens[SPT], part = 0;
+#pragma unroll
+            for (int i = 0; i < SPT; ++i) {
+                const int s = tid * SPT + i;
+                lens[i] = 0;
+                if (s < ns) {
+                    const int r = a.route_res[r0 + seg0 + s];
+                    const int k0 = a.cu_kept[r];
+                    const int beg = a.res_off ? a.res_off[(size_t)r * a.n_kv_heads + g] : k0;
+                    // rows past the end of the plane are not visited
+                    lens[i] = (int)max(0L, min((long)a.cu_kept[r + 1] - k0, a.k_rows - beg));
+                    sm.seg_row[s] = beg;
+                }
+                part += lens[i];
+            }
+            int run = block4_exclusive_scan(part, sm.scan, &s_vis);
+#pragma unroll
+            for (int i = 0; i < SPT; ++i) {
+                const int s = tid * SPT + i;
+                if (s < ns) sm.seg_start[s] = run;
+                run += lens[i];
+            }
+            if (tid == 0) sm.seg_start[ns] = s_vis;
         }
-        const int c0 = a.cu_ctx[unit];
-        const int tc = a.cu_ctx[unit + 1] - c0;
-        const int last = min(tc - q_len + row, (int)a.c_rows - 1 - c0);
-        const float* ckb = a.ck + ((size_t)g * a.c_rows + c0) * d;
-        const float* cvb = a.cv + ((size_t)g * a.c_rows + c0) * d;
-        for (int u = 0; u <= last; ++u) visit(ckb + (size_t)u * d, cvb + (size_t)u * d);
+        __syncthreads();
+        const int n_keys = s_vis + (last_pass ? max(0, block_last + 1) : 0);
+        const int n_tiles = (n_keys + kKeys - 1) / kKeys;
+        // stream positions up to these are visible to the column / to all columns
+        const int vis_hi = last_pass ? s_vis + my_last : s_vis - 1;
+        const int all_hi = last_pass ? s_vis + block_first : s_vis - 1;
+
+        // Row of this lane's key l32 of a tile: the segment plane's row, or
+        // ~row of the causal plane.  Keys past the stream repeat its last
+        // one.  A lane's segment index only moves forward.
+        int sidx = 0;
+        auto row_code = [&](int t) -> int {
+            const int p = min(t * kKeys + l32, n_keys - 1);
+            if (p >= s_vis) return ~max(0, min(c0 + (p - s_vis), (int)a.c_rows - 1));
+            while (sidx + 1 < ns && p >= sm.seg_start[sidx + 1]) ++sidx;
+            return max(0, min(sm.seg_row[sidx] + (p - sm.seg_start[sidx]), (int)a.k_rows - 1));
+        };
+        const float* seg_k = a.k + (size_t)g * a.k_gstride * HD;
+        const float* seg_v = a.v + (size_t)g * a.k_gstride * HD;
+        const float* ctx_k = a.ck + (size_t)g * a.c_rows * HD;
+        const float* ctx_v = a.cv + (size_t)g * a.c_rows * HD;
+
+        f32x4 kf[NJ];  // K tile (A operand): key l32, dims 8 j + 4 half + [0, 4)
+        int code = 0;
+        auto load_k = [&](int t) {
+            code = row_code(t);
+            const float* kp = (code < 0 ? ctx_k + (size_t)(~code) * HD : seg_k + (size_t)code * HD) + half * 4;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kp + j * 8);
+        };
+        auto copy_v = [&]() {  // of the tile whose row codes are in `code`
+#pragma unroll
+            for (int c = 0; c < NVC; ++c) {
+                // lane k holds key k's code (the byte address folds into the instruction)
+                const int rc_ = __builtin_amdgcn_ds_bpermute(lane / LPR * 4 + c * (256 / LPR), code);
+                const float* vp = rc_ < 0 ? ctx_v + (size_t)(~rc_) * HD : seg_v + (size_t)rc_ * HD;
+                __builtin_amdgcn_global_load_lds(vp + (lane % LPR) * 4, (lds_void*)(vbuf + c * 256), 16, 0, 0);
+            }
+        };
+
+        if (wave < n_tiles) load_k(wave);
+        for (int t = wave; t < n_tiles; t += kWaves) {
+            copy_v();
+            // two chains, added at the end: half the rounding of one long chain
+            f32x16 s0 = {}, s1 = {};
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (j & 1)
+                        s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], qf[j][e], s1, 0, 0, 0);
+                    else
+                        s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+                }
+            s0 += s1;
+            __builtin_amdgcn_sched_barrier(0);  // the K loads wait for the registers of this tile's
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the V tile is in LDS
+            asm volatile("" ::: "memory");
+            if (t + kWaves < n_tiles) load_k(t + kWaves);
+            const bool masked = t * kKeys + kKeys - 1 > all_hi;
+            const int rem = vis_hi - t * kKeys - half * 4;  // key offsets above it are masked
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s0[r] *= sc;
+            if (masked) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if ((r >> 2) * 8 + (r & 3) > rem) s0[r] = -INFINITY;
+            }
+            float mt = s0[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s0[r]);
+            mt = pair_max(mt);
+            if (__builtin_amdgcn_ballot_w64(mt > m)) {
+                const float mn = fmaxf(m, mt);
+                const float alpha = m == mn ? 1.f : exp2f(m - mn);  // 0 when m == -inf
+                l *= alpha;
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
+                m = mn;
+            }
+            const float mr = m == -INFINITY ? 0.f : m;  // a column that has seen no key yet
+            float ts = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                s0[r] = exp2f(s0[r] - mr);
+                ts += s0[r];
+            }
+            l += ts;
+            const float* vr = vbuf + half * 4 * HD + l32;
+            // A masked key weighs 0, but 0 times an infinity or NaN of its
+            // value row is no zero: in a masked tile that holds one, the
+            // product takes 0 in its place, and the columns that see the key
+            // add it afterwards.
+            uint32_t top = 0;  // largest magnitude in the tile
+            if (masked) {
+#pragma unroll 1
+                for (int i = 0; i < NVC; ++i) {
+                    const u32x4 w = *reinterpret_cast<const u32x4*>(vbuf + i * 256 + lane * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) top = max(top, w[e] & 0x7fffffffu);
+                }
+            }
+            const bool clean = __builtin_amdgcn_ballot_w64(top >= 0x7f800000u) != 0;
+            const uint32_t keep = clean ? 0x7f7fffffu : 0x7fffffffu;  // magnitudes that enter the product
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) {
+                    const float v = vr[((r >> 2) * 8 + (r & 3)) * HD + db * 32];
+                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                        (__float_as_uint(v) & 0x7fffffffu) <= keep ? v : 0.f, s0[r], oacc[db], 0, 0, 0);
+                }
+            if (__builtin_expect(clean, 0)) {
+                const int rem0 = min(vis_hi, n_keys - 1) - t * kKeys;
+#pragma unroll 1
+                for (int key = 0; key <= rem0 && key < kKeys; ++key)
+#pragma unroll
+                    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const float v = vbuf[key * HD + db * 32 + (r >> 2) * 8 + half * 4 + (r & 3)];
+                            oacc[db][r] += __builtin_isfinite(v) ? 0.f : v;
+                        }
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the V tile is read before the next copy
+            asm volatile("" ::: "memory");
+        }
+        if (last_pass) break;
     }
 
-    const float inv = 1.0f / acc.l;
-    float* op = a.out + ((size_t)(q_row0 + row) * a.n_q_heads + head) * d;
-    op[lane] = acc.o0 * inv;
-    if (two) op[lane + 64] = acc.o1 * inv;
-    if (a.lse && lane == 0)
-        a.lse[(size_t)head * a.lse_rows + q_row0 + row] =
-            (acc.m + log2f(acc.l)) * 0.69314718055994531f;
+    // ---- merge of the four waves: O rows in LDS (16-byte chunks swizzled by
+    // column), the two halves of a column's sum first
+    l = pair_sum(l);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int c = db * 8 + r4 * 2 + half;
+            *reinterpret_cast<f32x4*>(vbuf + l32 * HD + ((c ^ (l32 % LPR)) << 2)) =
+                f32x4{oacc[db][r4 * 4], oacc[db][r4 * 4 + 1], oacc[db][r4 * 4 + 2], oacc[db][r4 * 4 + 3]};
+        }
+    if (half == 0) {
+        sm.ml[wave][l32][0] = m;
+        sm.ml[wave][l32][1] = l;
+    }
+    __syncthreads();
+    for (int i = tid; i < used * LPR; i += kThreads) {
+        const int col = i / LPR, c = i % LPR;
+        const int j = j0 + col;
+        const long row = (long)q_row0 + j / R;
+        const int head = g * R + j % R;
+        if (row < 0 || row > max_q) continue;
+        float mx = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, sm.ml[w][col][0]);
+        f32x4 num = {0.f, 0.f, 0.f, 0.f};
+        float den = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            // a wave that saw no visible key carries no weight (its NaN sum,
+            // from a NaN logit, does)
+            const float mw = sm.ml[w][col][0], lw = sm.ml[w][col][1];
+            const float f = mw == -INFINITY ? (lw == 0.f ? 0.f : lw) : exp2f(mw - mx);
+            const f32x4 o = *reinterpret_cast<const f32x4*>(&sm.v[w][col * HD + ((c ^ (col % LPR)) << 2)]);
+            if (f != 0.f) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) num[e] += f * o[e];
+                den += f * lw;
+            }
+        }
+        const float inv = 1.0f / den;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) num[e] *= inv;
+        *reinterpret_cast<f32x4*>(a.out + ((size_t)row * a.n_q_heads + head) * HD + c * 4) = num;
+        if (a.lse && c == 0)
+            a.lse[(size_t)head * a.lse_rows + row] = (mx + log2f(den)) * 0.69314718055994531f;
+    }
 }
 
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnF32Args& a, bool encode, hipStream_t stream) {
-    const long waves = (long)a.max_rows * a.n_units * a.n_q_heads;
-    if (waves == 0) return hipSuccess;
-    const long blocks = (waves + 3) / 4;
+    AttnF32Args b = a;
+    b.max_rows = (int)std::min((long)a.max_rows, a.lse_rows);  // no unit has more rows
+    b.n_cb = (int)(((long)b.max_rows * a.ratio + kCols - 1) / kCols);
+    const long blocks = (long)b.n_cb * a.n_units * a.n_kv_heads;
+    if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    if (encode)
-        hipLaunchKernelGGL(attn_f32_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
-    else
-        hipLaunchKernelGGL(attn_f32_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+    const dim3 grid((unsigned)blocks), block(kThreads);
+    if (a.head_dim == 128) {
+        if (encode)
+            hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, block, 0, stream, b);
+        else
+            hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, block, 0, stream, b);
+    } else {
+        if (encode)
+            hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, block, 0, stream, b);
+        else
+            hipLaunchKernelGGL((attn_f32_kernel<64, false>), grid, block, 0, stream, b);
+    }
     return hipGetLastError();
 }
 

@@ -59,7 +59,8 @@ int attend_block_rows(int ratio);
 // fp32 reference-precision attention (encode or conversation attend).
 struct AttnF32Args {
     int n_q_heads, n_kv_heads, ratio, head_dim;
-    int n_units, max_rows;  // grid: max_rows x n_units x n_q_heads waves
+    int n_units, max_rows;
+    int n_cb;  // 32-column blocks per (unit, group): the launcher fills it from max_rows * ratio
     float scale;
     const float* q;
     float* out;
