@@ -14,10 +14,13 @@
 // off = S_vis + Tc - Tq.  Both are a list of segments followed by a causal
 // part, and share one code path.
 //
-// Work decomposition.  A workgroup is NW waves (4 in encode, 8 in prefill)
-// that share one KV group and NW (query head, 32-row block) pairs of it (hpw
-// heads x rbw row blocks, hpw the largest power of two up to NW dividing the
-// group size); each wave owns one pair and computes the transposed products
+// Work decomposition.  The (32-row block, query head) pairs of a unit and KV
+// group are numbered row block first, and a group of NW waves that share its
+// K / V tiles takes NW consecutive ones, whatever the group size (28 / 4 heads:
+// a block of NW row blocks of one head spanned 32 NW rows, every wave running
+// the tiles up to the last; a catalogue of 40 resources of 30 to 900 tokens
+// after a 300-token prefix takes 271 us instead of 301); each wave owns one
+// pair and computes the transposed products
 //     S^T = K Q^T    (32x32x16 bf16 MFMA; A = K rows from LDS, B = Q^T in VGPRs)
 //     O^T += V^T P^T (A = V^T from LDS, B = P^T straight from the S^T accumulators)
 // so that each lane owns exactly one query row in both accumulators: row max
@@ -46,8 +49,10 @@
 // Tiles never cross a resource boundary in encode, and the reduction order
 // depends only on local indices, so a resource's outputs are bit-identical
 // wherever it is packed and whatever its neighbours are.
+#include <algorithm>
 #include <utility>
 
+#include "attn_tile.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -66,15 +71,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 constexpr int kBK = 64;  // keys per tile
-// A lane's sum of a tile's weights above this moves the reference max.
-constexpr float kWeightCap = 65536.0f;  // 2^16
-constexpr int kMaxSeg = 1024;
-// Third dword of a gfx9 buffer resource for raw (unformatted) loads.
-constexpr int kBufferFlags = 0x00020000;
-
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
 template <int HD, int NW>
 struct Tile {
     static constexpr int CPR = HD / 8;           // 16-byte chunks per row
@@ -114,57 +110,17 @@ struct Smem {
     int scan[NW];  // wave totals of the segment-length scan
 };
 
-// XOR mask of a row's chunk index: for 256-byte rows the two 2-bit halves of
-// row % 16 are swapped, which keeps the 16 rows of an A-operand read on 16
-// distinct chunks and puts the four rows of one transpose-read lane group on
-// four distinct 4-chunk groups (both bank-conflict free, as measured with the
-// LDS conflict counter).
-template <int CPR>
-__device__ __forceinline__ int chunk_mask(int row) {
-    return CPR == 16 ? (((row & 3) << 2) | ((row >> 2) & 3)) : (row % CPR);
-}
-
-template <int HD>
-__device__ __forceinline__ uint32_t swz(int row, int chunk) {
-    constexpr int CPR = HD / 8;
-    return (uint32_t)(row * HD * 2 + ((chunk ^ chunk_mask<CPR>(row)) << 4));
-}
-
 __device__ __forceinline__ void wait_vm0() {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt / lgkmcnt unconstrained
 }
 
-// Rows a block is responsible for but cannot compute (its route list is
-// longer than the segment table, or they lie past the query rows the grid
-// was sized for): NaN in out and lse, so that a caller's size error shows in
-// the outputs instead of leaving rows unwritten or dropping resources.
-// Rows [r_begin, r_end) of unit rows starting at q_row0, heads
-// [head0, head0 + n_heads).
-template <int HD, int NW>
-__device__ __forceinline__ void poison_rows(const AttnArgs& a, int head0, int n_heads, int q_row0,
-                                         int r_begin, int r_end) {
-    constexpr int CPR = HD / 8;
-    const u32x4 nan8 = {0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u};  // bf16 NaNs
-    const long n = (long)max(r_end - r_begin, 0) * n_heads * CPR;
-    for (long i = threadIdx.x; i < n; i += NW * 64) {
-        const int c = (int)(i % CPR);
-        const long rest = i / CPR;
-        const int h = head0 + (int)(rest % n_heads);
-        const long row = (long)q_row0 + r_begin + rest / n_heads;
-        if (row < 0 || row >= a.lse_rows) continue;
-        *reinterpret_cast<u32x4*>(a.out + ((size_t)row * a.n_q_heads + h) * HD + c * 8) = nan8;
-        if (c == 0 && a.lse) a.lse[(size_t)h * a.lse_rows + row] = __builtin_nanf("");
-    }
-}
-
-// NW waves per block, each owning one (query head, 32-row block) pair of the
-// block's KV group; two waves per SIMD either way (two 4-wave blocks or one
-// 8-wave block per CU).
+// NW waves per block, each owning one (row block, query head) pair; two waves
+// per SIMD either way (two 4-wave blocks or one 8-wave block per CU).
 template <int HD, bool ENCODE, int NW>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnArgs a) {
     using TL = Tile<HD, NW>;
     constexpr int kThreads = NW * 64;
-    constexpr int ROWB = TL::ROWB, TILEB = TL::TILEB, STAGEB = TL::STAGEB;
+    constexpr int ROWB = TL::ROWB, TILEB = TL::TILEB;
     __shared__ Smem<ENCODE, NW> sm;
     __shared__ __attribute__((aligned(16))) char k_st0[TILEB], k_st1[TILEB], v_st0[TILEB], v_st1[TILEB];
 
@@ -173,17 +129,15 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: a scalar
     const int l32 = lane & 31, half = lane >> 5;
 
-    // block -> (unit, head slice, q tile [longest first], group).  The group
-    // is the fastest index, so the blocks of one group land on one XCD, and
-    // the q tiles of a (unit, group) come next, so the blocks that run side
-    // by side on an XCD stream the same keys through its L2.
+    // block -> (unit, pairs [longest first], group).  The group is the
+    // fastest index, so the blocks of one group land on one XCD, and the
+    // pairs of a (unit, group) come next, so the blocks that run side by side
+    // on an XCD stream the same keys through its L2.
     int bid = blockIdx.x;
     int g = bid % a.n_kv_heads;
     bid /= a.n_kv_heads;
-    const int jt = a.n_qt - 1 - bid % a.n_qt;
-    bid /= a.n_qt;
-    const int hq = bid % a.n_hq;
-    int unit = bid / a.n_hq;
+    const int pair0 = (a.n_qt - 1 - bid % a.n_qt) * NW;  // the block's first pair
+    int unit = bid / a.n_qt;
     if constexpr (!ENCODE) {
         if (a.plan) {
             // Prefill with a work order: grid position (unit, g) takes the
@@ -223,16 +177,21 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
         ctx_row0 = a.cu_ctx[unit];
         tc = a.cu_ctx[unit + 1] - ctx_row0;
     }
-    const int wg_rows = 32 * a.rbw;
-    const int q_first = jt * wg_rows;
-    // the grid covers query rows [0, n_qt * wg_rows) of every unit; the block
-    // of the last tile answers for any rows beyond
-    if (jt == a.n_qt - 1 && q_len > a.n_qt * wg_rows) {
-        poison_rows<HD, NW>(a, g * a.ratio + hq * a.hpw, a.hpw, q_row0, q_first, q_len);
-        return;
+    // this wave's pair, and the rows of the block
+    const int R = a.ratio;
+    const int rb = (pair0 + wave) / R, head = g * R + (pair0 + wave) % R;
+    const int rb_first = pair0 / R, rb_last = min((pair0 + NW - 1) / R, a.n_rb - 1);
+    const int q_first = rb_first * 32;
+    // The grid covers n_rb row blocks of every unit.  Where a unit has more
+    // rows, the waves of the last row block answer for them (and for their
+    // own rows, which are then not computed).
+    int q_lim = q_len;
+    if (q_len > a.n_rb * 32) {
+        q_lim = (a.n_rb - 1) * 32;
+        if (rb == a.n_rb - 1) poison_rows<HD>(a, head, 1, q_row0, q_lim, q_len, lane, 64);
     }
-    if (q_first >= q_len) return;
-    const int q_last = min(q_first + wg_rows, q_len) - 1;
+    if (q_first >= q_lim) return;
+    const int q_last = min(rb_last * 32 + 32, q_len) - 1;
 
     if constexpr (!ENCODE) {
         // Visible segments of this (request, layer, group): kept rows of the
@@ -241,7 +200,8 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
         const int r0 = a.route_off[e];
         n_seg = a.route_off[e + 1] - r0;
         if (n_seg > kMaxSeg) {
-            poison_rows<HD, NW>(a, g * a.ratio + hq * a.hpw, a.hpw, q_row0, q_first, q_last + 1);
+            if (rb < a.n_rb)
+                poison_rows<HD>(a, head, 1, q_row0, rb * 32, min(rb * 32 + 32, q_lim), lane, 64);
             return;
         }
         constexpr int SPT = kMaxSeg / kThreads;  // segments per thread
@@ -273,8 +233,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
     stream = s_vis + tc;
     const int n_tiles = (off + q_last) / kBK + 1;
 
-    const int head = g * a.ratio + hq * a.hpw + (wave % a.hpw);
-    const int my_q = q_first + (wave / a.hpw) * 32 + l32;
+    const int my_q = rb * 32 + l32;
     // rows outside [0, lse_rows) of q / out are never touched
     const int my_q_c = max(0, min(min(my_q, q_len - 1), (int)a.lse_rows - 1 - q_row0));
 
@@ -459,19 +418,19 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
         u32x4* raw = qraw;
         if constexpr (ENCODE) {
             // RoPE at the resource-local position; the pairs (f, f + HD/2) are
-            // (t, t + NT/2) in this lane.  For blocks of 32 rows (4 heads) the
+            // (t, t + NT/2) in this lane.  For blocks of one row block the
             // cos / sin of the block's rows are computed once into LDS, in the
             // V buffer of stage 1, which no copy touches before the loop: row
             // r, frequency f sits in 16-byte chunk (f / 2) ^ (r % 16) of the
             // row, so the 16 rows read by a lane group fall on distinct banks.
-            // Larger blocks compute their lane's 32 frequencies directly.
+            // Other blocks compute their lane's 32 frequencies directly.
             constexpr int HALF = HD / 2;
             const char* tab = v_st1;
-            const bool use_tab = wg_rows <= 32;
-            const int r = my_q - q_first;
+            const bool use_tab = rb_first == rb_last;
+            const int r = l32;
             if (use_tab) {
                 char* wtab = v_st1;
-                for (int idx = tid; idx < wg_rows * HALF; idx += kThreads) {
+                for (int idx = tid; idx < 32 * HALF; idx += kThreads) {
                     const int rr = idx / HALF, f = idx % HALF;
                     float sn, cs;
                     sincos_rev_fast(rope_revolutions(pos0 + min(q_first + rr, q_len - 1), a.rope.rev[f]),
@@ -727,17 +686,17 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_wave_barrier();
         constexpr int RPS = 64 / CPR;  // rows per store instruction
-        const int q_base = q_first + (wave / a.hpw) * 32;
+        const int q_base = rb * 32;
 #pragma unroll
         for (int it = 0; it < 32 / RPS; ++it) {
             const int r = it * RPS + ln / CPR, c = ln % CPR;
             const u32x4 v = *reinterpret_cast<const u32x4*>(ob + r * ROWB + ((c ^ (r % CPR)) << 4));
             const int q = q_base + r;
-            if (q < q_len && q_row0 + q < a.lse_rows)
+            if (q < q_lim && q_row0 + q < a.lse_rows)
                 *reinterpret_cast<u32x4*>(a.out + ((size_t)(q_row0 + q) * a.n_q_heads + head) * HD + c * 8) = v;
         }
         const int q = q_base + row;
-        if (a.lse && hf == 0 && q < q_len && q_row0 + q < a.lse_rows)
+        if (a.lse && hf == 0 && q < q_lim && q_row0 + q < a.lse_rows)
             a.lse[(size_t)head * a.lse_rows + q_row0 + q] = m * sl2 * 0.69314718055994531f + logf(l);
     }
 }
@@ -753,33 +712,15 @@ namespace {
 constexpr int kEncodeWaves = 4;
 constexpr int kAttendWaves = 8;
 
-// A block covers NW (query head, 32-row block) pairs of one KV group: hpw
-// heads x rbw row blocks, hpw the largest power of two up to NW dividing the
-// group size, so every head of the group is covered exactly once.
-template <int NW>
-int block_rows(int ratio) {
-    int h = NW;
-    while (ratio % h) h >>= 1;
-    return 32 * (NW / h);
-}
-
-template <int NW>
-void set_tiling(AttnArgs& b) {
-    int h = NW;
-    while (b.ratio % h) h >>= 1;
-    b.hpw = h;
-    b.rbw = NW / h;
-    b.n_hq = b.ratio / h;
-    b.n_qt = (b.max_rows + 32 * b.rbw - 1) / (32 * b.rbw);
-}
-
 template <int HD, bool ENCODE, int NW>
 hipError_t launch(const AttnArgs& a, hipStream_t stream) {
     AttnArgs b = a;
-    set_tiling<NW>(b);
-    const long blocks = (long)b.n_qt * b.n_units * b.n_hq * b.n_kv_heads;
+    b.n_rb = (int)(((long)a.max_rows + 31) / 32);
+    const long pairs = (long)b.n_rb * a.ratio;
+    const long blocks = (pairs + NW - 1) / NW * b.n_units * b.n_kv_heads;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+    b.n_qt = (int)((pairs + NW - 1) / NW);
     hipLaunchKernelGGL((attn_mfma_kernel<HD, ENCODE, NW>), dim3((unsigned)blocks), dim3(NW * 64), 0,
                        stream, b);
     return hipGetLastError();
@@ -787,7 +728,14 @@ hipError_t launch(const AttnArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-int attend_block_rows(int ratio) { return ratio >= 1 ? block_rows<kAttendWaves>(ratio) : 0; }
+// The work order's unit of prefill work: 32 * 8 / h rows, h the largest power
+// of two up to 8 that divides the group size.
+int attend_block_rows(int ratio) {
+    if (ratio < 1) return 0;
+    int h = 8;
+    while (ratio % h) h >>= 1;
+    return 32 * (8 / h);
+}
 
 hipError_t launch_attn_mfma(const AttnArgs& a, bool encode, int head_dim, hipStream_t stream) {
     if (a.ratio < 1 || a.max_rows < 1) return hipErrorInvalidValue;

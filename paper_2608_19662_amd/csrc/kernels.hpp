@@ -12,14 +12,12 @@ namespace rc {
 
 // bf16 MFMA flash attention (encode or conversation prefill).
 struct AttnArgs {
-    // decomposition: blocks = n_qt * n_units * n_hq * n_kv_heads; the
-    // launcher fills hpw, rbw, n_hq and n_qt from ratio and max_rows
+    // decomposition: blocks = n_qt * n_units * n_kv_heads; the launchers fill
+    // n_rb and n_qt from ratio and max_rows
     int n_q_heads, n_kv_heads, ratio;
-    int hpw;      // query heads per block (largest power of two <= waves dividing ratio)
-    int rbw;      // 32-row blocks per block (waves / hpw: one (head, row block) pair per wave)
-    int n_hq;     // blocks per group along heads (ratio / hpw)
+    int n_rb;     // 32-row blocks per unit
+    int n_qt;     // blocks per (unit, KV group)
     int n_units;  // resources (encode) or requests (prefill)
-    int n_qt;     // query tiles per unit (ceil(max_rows / (32 * rbw)))
     float scale_log2;  // softmax_scale * log2(e)
     const uint16_t* q;
     uint16_t* out;
