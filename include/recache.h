@@ -247,8 +247,8 @@ int recache_store_routes(int dtype, int layer, int n_layers, int n_res, const in
  * outputs and log-sum-exps are merged afterwards; the workspace holds those
  * partials, fp32, n_req * n_q_heads * splits * (head_dim + 2) values.
  * max_kv is an upper bound on the keys a (request, group) can see in one layer
- * (route tokens + context), used only to choose the split count; 0 means
- * "use max_ctx".  Returns 0 for invalid sizes.  Pure host arithmetic.
+ * (route tokens + context), used only to choose the split count (and by
+ * prefill the form of its blocks); 0 means "use max_ctx" (prefill: unknown).  Returns 0 for invalid sizes.  Pure host arithmetic.
  */
 size_t recache_attend_workspace_bytes(int n_req, int max_q, int max_ctx, int max_kv,
                                       int n_q_heads, int n_kv_heads, int head_dim);

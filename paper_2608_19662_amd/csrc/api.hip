@@ -542,6 +542,7 @@ int recache_attend_cached(int dtype, int layer, int n_layers, int n_req, const i
     a.route_res = route_res;
     a.cu_kept = cu_kept;
     a.plan = plan;
+    a.max_keys = max_kv;
     return hip_status(launch_attn_mfma(a, false, head_dim, s), "attend (prefill) launch");
 }
 

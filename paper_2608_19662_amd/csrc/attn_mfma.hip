@@ -705,12 +705,10 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
 
 namespace {
 
-// Waves per block of each mode: encode's blocks are short (a few tiles per
-// resource), so two 4-wave blocks per CU overlap one block's prologue with
-// the other's loop; prefill streams long key lists, where one 8-wave block
-// per CU copies each K / V tile once for twice the query rows.
+// Waves per block of encode: its blocks are short (a few tiles per resource),
+// so two 4-wave blocks per CU overlap one block's prologue with the other's
+// loop.
 constexpr int kEncodeWaves = 4;
-constexpr int kAttendWaves = 8;
 
 template <int HD, bool ENCODE, int NW>
 hipError_t launch(const AttnArgs& a, hipStream_t stream) {
@@ -737,13 +735,55 @@ int attend_block_rows(int ratio) {
     return 32 * (8 / h);
 }
 
+namespace {
+
+// Form of a prefill launch: "split" is attn_split.hip with 4 or 8 waves,
+// "blocks" this file's kernel with 4 or 8.  By the number of 32-column blocks
+// that the queries make over all requests and KV groups (32 / 8 heads,
+// head_dim 128, 4,000 resource rows and 2,000 of context unless said; us):
+//   <= 256, one 8-wave split block per CU: at 64 blocks split 8 waves 43, 4
+//       waves 63, blocks of 4 waves 118, of 8 150; at 256: 54, 74, 136, 180
+//   <= 512, two 4-wave split blocks per CU: at 448 split 4 waves 84, 8 waves
+//       91, blocks of 4 waves 129.  Past it the split's own K / V reads cost
+//       more than idle CUs: at 640 split 4 waves 141, blocks of 4 waves 125
+//   more: split with 4 waves still where a request's columns fill one block
+//       or less, so that nothing is read twice (128 requests of 4 queries over
+//       2,000 keys: 123, blocks of 4 waves 150, of 8 253); else blocks of
+//   8 waves where the grid fills the GPU and the streams are long, so that
+//       each K / V tile is copied once for twice the rows (64 / 8 heads, 4,096
+//       blocks: 417 against 430), or where one such block holds all pairs of a
+//       request and group, which take two of 4 waves (28 / 4 heads, 128
+//       requests of 16 queries over 2,000 keys: 136 against 146);
+//   4 waves otherwise, two blocks per CU overlapping prologue and loop (1,024
+//       blocks: 98 against 128; 16,384 over 3,226 keys: 431 against 464; 4,544
+//       over 600 keys: 36 against 42).
+// A full grid with no bound on its keys (0) takes 8 waves.
+enum class PrefillForm { kSplit8, kSplit4, kBlocks4, kBlocks8 };
+
+PrefillForm prefill_form(const AttnArgs& a) {
+    const long col_blocks =
+        std::max((a.lse_rows * a.ratio + 31) / 32, (long)a.n_units) * a.n_kv_heads;
+    if (col_blocks <= 256) return PrefillForm::kSplit8;
+    if (col_blocks <= 512 || (long)a.max_rows * a.ratio <= 32) return PrefillForm::kSplit4;
+    if (col_blocks >= 2048 && (a.max_keys <= 0 || a.max_keys >= 4096)) return PrefillForm::kBlocks8;
+    if (a.max_rows <= 32 && a.ratio > 4) return PrefillForm::kBlocks8;
+    return PrefillForm::kBlocks4;
+}
+
+}  // namespace
+
 hipError_t launch_attn_mfma(const AttnArgs& a, bool encode, int head_dim, hipStream_t stream) {
     if (a.ratio < 1 || a.max_rows < 1) return hipErrorInvalidValue;
-    if (head_dim == 128)
-        return encode ? launch<128, true, kEncodeWaves>(a, stream)
-                      : launch<128, false, kAttendWaves>(a, stream);
-    return encode ? launch<64, true, kEncodeWaves>(a, stream)
-                  : launch<64, false, kAttendWaves>(a, stream);
+    if (encode)
+        return head_dim == 128 ? launch<128, true, kEncodeWaves>(a, stream)
+                               : launch<64, true, kEncodeWaves>(a, stream);
+    switch (prefill_form(a)) {
+        case PrefillForm::kSplit8: return launch_attn_split(a, head_dim, 8, stream);
+        case PrefillForm::kSplit4: return launch_attn_split(a, head_dim, 4, stream);
+        case PrefillForm::kBlocks4:
+            return head_dim == 128 ? launch<128, false, 4>(a, stream) : launch<64, false, 4>(a, stream);
+        default: return head_dim == 128 ? launch<128, false, 8>(a, stream) : launch<64, false, 8>(a, stream);
+    }
 }
 
 }  // namespace rc

@@ -1,0 +1,420 @@
+// bf16 conversation prefill for small grids: few requests or few queries,
+// where blocks that own whole key streams leave most of the GPU idle.
+// Visibility, key stream and softmax are those of the prefill kernel
+// (attn_mfma.hip); what differs is the decomposition.
+//
+// The query rows of a request and KV group are flattened to columns
+// j = row * ratio + head; a block owns 32 of them, and its W waves take the
+// 32-key tiles of the stream in turn, each with its own softmax state and
+// pipeline (no barriers in the loop), merged in LDS at the end.  A stream of
+// n keys then costs a block n / (32 W) tiles instead of n / 64, and a group's
+// blocks number rows * ratio / 32 instead of rows * ratio / 256.  What it
+// gives up is sharing: every wave reads its own K and V (16 KB per tile of
+// 16 MFMAs), so a full grid would run at the L2's 64 B/clk per CU, about half
+// of the matrix rate.  The launcher's rule weighs the two.
+//
+// Per tile (32 keys):
+//     S^T = K Q^T      (32x32x16 bf16 MFMA; A = K rows from LDS, B = Q^T in VGPRs)
+//     O^T += V^T P^T   (A = V^T by LDS transpose reads, B = P^T from the S^T
+//                       accumulators)
+// K and V go straight into LDS.  (K fragments loaded into VGPRs touch 32 rows
+// with 32 bytes each per load: 46 us against 32 at 64 queries, 4,000 keys.)
+#include <algorithm>
+
+#include "attn_tile.hpp"
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace rc {
+
+namespace {
+
+constexpr int kCols = 32;  // columns (row, head) per block
+constexpr int kKeys = 32;  // keys per wave tile
+
+template <int W>
+struct SplitSmem {
+    int seg_start[kMaxSeg + 1];
+    int seg_row[kMaxSeg];
+    int scan[W];
+    float ml[W][kCols][2];
+};
+
+template <int HD, int W>
+__global__ __launch_bounds__(W * 64, 2) void attn_split_kernel(const AttnArgs a) {
+    constexpr int kThreads = W * 64;
+    constexpr int CPR = HD / 8;        // 16-byte chunks per row
+    constexpr int ROWB = HD * 2;       // bytes per row
+    constexpr int NT = HD / 16;        // MFMA k-steps over head_dim
+    constexpr int NDB = HD / 32;       // 32-wide blocks of head_dim
+    constexpr int RPI = 64 / CPR;      // rows per 1 KB wave copy
+    constexpr int NJ = kKeys / RPI;    // copies per V tile
+    constexpr int NP = CPR == 16 ? 4 : 1;  // copy j's swizzle repeats with this period
+    constexpr int TILEB = kKeys * ROWB;
+    __shared__ SplitSmem<W> sm;
+    // Per wave one K and one V tile (two arrays: the compiler then sees that
+    // copies in flight into one do not touch the other); after the loop the
+    // lower and upper dims of the wave's O, fp32 [32 columns][HD / 2] each.
+    __shared__ __attribute__((aligned(16))) char k_st[W][TILEB], v_st[W][TILEB];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int R = a.ratio;
+
+    // block -> (unit, column block [longest first], group), as in the prefill
+    // kernel: the blocks of one (request, group) run side by side on one XCD
+    int bid = blockIdx.x;
+    int g = bid % a.n_kv_heads;
+    bid /= a.n_kv_heads;
+    const int cb = a.n_qt - 1 - bid % a.n_qt;
+    int unit = bid / a.n_qt;
+    if (a.plan) {
+        const int n_pairs = a.n_units * a.n_kv_heads;
+        int p = a.plan[(size_t)a.layer * n_pairs + unit * a.n_kv_heads + g];
+        p = min(max(p, 0), n_pairs - 1);  // in bounds whatever the plan holds
+        unit = p / a.n_kv_heads;
+        g = p % a.n_kv_heads;
+    } else {
+        g = (g + unit) % a.n_kv_heads;
+    }
+    const int q_row0 = a.cu_q[unit], q_len = a.cu_q[unit + 1] - q_row0;
+    const int c0 = a.cu_ctx[unit], tc = a.cu_ctx[unit + 1] - c0;
+    // the grid covers max_rows rows; the last block answers for any beyond
+    if (cb == a.n_qt - 1 && q_len > a.max_rows)
+        poison_rows<HD>(a, g * R, R, q_row0, a.max_rows, q_len, tid, kThreads);
+    const int j0 = cb * kCols, n_cols = min(q_len, a.max_rows) * R;
+    if (j0 >= n_cols) return;
+    const int used = min(kCols, n_cols - j0);
+    const int my_j = j0 + min(l32, used - 1);  // spare lanes repeat the last column
+    const int my_row = my_j / R, my_head = g * R + my_j % R;
+    const int first_row = j0 / R, last_row = (j0 + used - 1) / R;
+
+    // ---- Q^T (B operand): dims t*16 + half*8 + [0, 8) of this lane's column
+    bf16x8 qf[NT];
+    {
+        const long row = max(0L, min((long)q_row0 + my_row, a.lse_rows - 1));
+        const uint16_t* qp = a.q + ((size_t)row * a.n_q_heads + my_head) * HD + half * 8;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            qf[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + t * 16));
+    }
+
+    // ---- visible segments of this (request, layer, group)
+    const size_t e = ((size_t)unit * a.n_layers + a.layer) * a.n_kv_heads + g;
+    const int r0 = a.route_off[e];
+    const int n_seg = a.route_off[e + 1] - r0;
+    if (n_seg > kMaxSeg) {
+        for (int j = j0 + wave; j < j0 + used; j += W)
+            poison_rows<HD>(a, g * R + j % R, 1, q_row0, j / R, j / R + 1, lane, 64);
+        return;
+    }
+    int s_vis;
+    {
+        constexpr int SPT = kMaxSeg / kThreads;
+        int lens[SPT], part = 0;
+#pragma unroll
+        for (int i = 0; i < SPT; ++i) {
+            const int s = tid * SPT + i;
+            lens[i] = 0;
+            if (s < n_seg) {
+                const int r = a.route_res[r0 + s];
+                const int k0 = a.cu_kept[r];
+                lens[i] = a.cu_kept[r + 1] - k0;
+                sm.seg_row[s] = a.res_off ? a.res_off[(size_t)r * a.n_kv_heads + g] : k0;
+            }
+            part += lens[i];
+        }
+        int run = block_exclusive_scan<W>(part, sm.scan, &s_vis);
+#pragma unroll
+        for (int i = 0; i < SPT; ++i) {
+            const int s = tid * SPT + i;
+            if (s < n_seg) sm.seg_start[s] = run;
+            run += lens[i];
+        }
+        if (tid == 0) sm.seg_start[n_seg] = s_vis;
+        // a scalar, so that what is chosen by it below is seen to be uniform
+        s_vis = __builtin_amdgcn_readfirstlane(s_vis);
+    }
+    __syncthreads();
+    // Tiles: the segment rows' 32 at a time, then the causal rows', so that
+    // every tile has its rows in one plane.
+    const int off = tc - q_len;                          // a column sees causal rows <= off + row
+    const int n_ctx = max(0, min(off + last_row + 1, tc));  // causal rows the block sees
+    const int n_segt = (s_vis + kKeys - 1) / kKeys;
+    const int n_tiles = n_segt + (n_ctx + kKeys - 1) / kKeys;
+
+    // ---- HBM -> LDS copies.  Two planes (segment rows, causal rows), each a
+    // buffer resource for K and one for V: a load past a plane's end returns
+    // zeros.  A tile of consecutive rows takes their offset in a scalar
+    // register plus per-lane constants; any other tile looks its keys up, key
+    // l32 per lane, and its copies fetch the row offsets from those lanes.
+    // Copy j moves rows j*RPI + [0, RPI); lane i lands at byte 16 i of them,
+    // chunk i % CPR, which holds logical chunk (i % CPR) ^ mask(row).
+    // The resource is formed at each copy from values pinned to scalar
+    // registers: one in vector registers would cost every copy a loop.
+    auto plane = [&](bool is_v, bool causal) {
+        const uint16_t* p = causal ? (is_v ? a.cv : a.ck) : (is_v ? a.v : a.k);
+        const uint64_t u = (uint64_t)(p + (size_t)g * (causal ? a.c_rows : a.k_gstride) * HD);
+        const uint64_t base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
+                              (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
+        const int bytes = __builtin_amdgcn_readfirstlane((int)((causal ? a.c_rows : a.k_rows) * ROWB));
+        return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, bytes, kBufferFlags);
+    };
+    const int v_row = lane / CPR;  // row of this lane in a copy
+    u32x4 lane_off;                // its byte offset in copy j % NP, from the copy's first row
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        lane_off[j] = (uint32_t)(v_row * ROWB + (((lane % CPR) ^ chunk_mask<CPR>(j % NP * RPI + v_row)) << 4));
+    bool causal = true;   // the plane of the tile being copied
+    bool t_fast = false;  // its rows are consecutive:
+    uint32_t t_off = 0;   // the first one's byte offset
+    uint32_t key_off = 0; // else this lane's key l32: its row's byte offset
+    int u_i = 0, u_hi = 0, u_dl = 0;   // wave-uniform segment walk
+    int sidx = 0, s_hi = 0, s_dl = 0;  // this lane's segment walk
+    if (n_seg > 0) {
+        u_hi = __builtin_amdgcn_readfirstlane(sm.seg_start[1]);
+        u_dl = __builtin_amdgcn_readfirstlane(sm.seg_row[0]);
+        s_hi = u_hi;
+        s_dl = u_dl;
+    }
+    auto set_tile = [&](int t) {
+        long row;
+        if (t < n_segt) {
+            const int p0 = t * kKeys;
+            while (p0 >= u_hi && u_i + 1 < n_seg) {
+                ++u_i;
+                u_hi = __builtin_amdgcn_readfirstlane(sm.seg_start[u_i + 1]);
+                u_dl = __builtin_amdgcn_readfirstlane(sm.seg_row[u_i]) -
+                       __builtin_amdgcn_readfirstlane(sm.seg_start[u_i]);
+            }
+            causal = false;
+            row = (long)u_dl + p0;
+            t_fast = p0 + kKeys <= u_hi && row >= 0 && row + kKeys <= a.k_rows;
+            if (!t_fast) {
+                const int p = min(p0 + l32, s_vis - 1);  // keys past the end repeat the last one
+                while (p >= s_hi && sidx + 1 < n_seg) {
+                    ++sidx;
+                    s_hi = sm.seg_start[sidx + 1];
+                    s_dl = sm.seg_row[sidx] - sm.seg_start[sidx];
+                }
+                key_off = (uint32_t)(s_dl + p) * ROWB;
+            }
+        } else {
+            const int p0 = (t - n_segt) * kKeys;
+            causal = true;
+            row = (long)c0 + p0;
+            t_fast = p0 + kKeys <= n_ctx && row >= 0 && row + kKeys <= a.c_rows;
+            key_off = (uint32_t)(c0 + min(p0 + l32, n_ctx - 1)) * ROWB;
+        }
+        t_off = (uint32_t)row * ROWB;
+    };
+    auto copy = [&](bool is_v, char* dst) {
+        const __amdgpu_buffer_rsrc_t r = plane(is_v, causal);
+        const uint32_t off0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t_off);
+        if (__builtin_amdgcn_readfirstlane((int)t_fast)) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(dst + j * 1024), 16, (int)lane_off[j % NP],
+                                                         (int)(off0 + j * RPI * ROWB), 0, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const uint32_t vo = (uint32_t)__builtin_amdgcn_ds_bpermute(v_row * 4 + j * RPI * 4, (int)key_off) +
+                                    (lane_off[j % NP] - (uint32_t)(v_row * ROWB));
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(dst + j * 1024), 16, (int)vo, 0, 0, 0);
+            }
+        }
+    };
+
+    // K as the A operand: key l32, chunk 2t + half (t moves chunk bits 1..3)
+    const uint32_t k_rd0 = swz<HD>(l32, half);
+    // V^T transpose-read offset (see attn_mfma.hip): rows s*16 + w*8 + half*4
+    // + [0, 4), the keys that P^T holds in slots w*4 + [0, 4) of step s
+    uint32_t v_rd0;
+    {
+        const int G = lane >> 4, i = lane & 15;
+        const int row = (G >> 1) * 4 + (i >> 2);
+        const int col = (G & 1) * 16 + (i & 3) * 4;
+        v_rd0 = swz<HD>(row, col >> 3) + (col & 7) * 2;
+    }
+    auto v_rd = [&](int db, int w) -> uint32_t {
+        return v_rd0 ^ (uint32_t)(db << 6) ^ (uint32_t)(w * (8 * ROWB + (CPR == 16 ? 32 : 0)));
+    };
+
+    const float sl2 = a.scale_log2;
+    const bf16x2 ones2 = __builtin_bit_cast(bf16x2, 0x3F803F80u);  // (1.0, 1.0) in bf16
+    float m = kNoKey, lsum = 0.f;
+    f32x16 oacc[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) oacc[db] = f32x16{};
+
+    // This wave's tiles are wave, wave + W, ...; only it touches its buffers,
+    // so waiting for its own copies is enough.  K(t + W) is copied behind the
+    // reads of K(t), V(t + W) behind those of V(t): one of the two is in
+    // flight at any time, and the block's other waves fill the waits.
+    constexpr int WAIT_OLD = NJ | 0x0F70;  // vmcnt(NJ): all but the newest tile copy
+    static_assert(NJ < 16, "vmcnt(NJ) fits the low counter bits");
+    char* kb = k_st[wave];
+    char* vb = v_st[wave];
+    if (wave < n_tiles) {
+        set_tile(wave);
+        copy(false, kb);
+        copy(true, vb);
+    }
+    // (the loop ends from its middle, so that on its back edge a V copy always
+    // follows the K copy: the compiler's own waits then count as these do)
+    for (int t = wave; wave < n_tiles; t += W) {
+        const bool more = t + W < n_tiles;
+        __builtin_amdgcn_s_waitcnt(WAIT_OLD);  // K(t)
+        f32x16 sc = {};
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const bf16x8 av = *reinterpret_cast<const bf16x8*>(kb + (k_rd0 ^ (i << 5)));
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qf[i], sc, 0, 0, 0);
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K(t) is read
+        if (more) {
+            set_tile(t + W);
+            copy(false, kb);
+        }
+        // key offsets that every column of the block sees, and this lane's
+        const int p0 = (t < n_segt ? t : t - n_segt) * kKeys;
+        if (kKeys - 1 > (t < n_segt ? s_vis - 1 : off + first_row) - p0) {
+            const int rem = (t < n_segt ? s_vis - 1 : off + my_row) - p0 - half * 4;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if ((r >> 2) * 8 + (r & 3) > rem) sc[r] = -INFINITY;
+        }
+        bf16x8 pf[2];
+        float tsum;
+        auto weights = [&]() {
+            const float msl = m * sl2;
+            tsum = 0.f;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                uint32_t w[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[8 * s + 2 * i], sl2, -msl));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[8 * s + 2 * i + 1], sl2, -msl));
+                    w[i] = pack_bf16x2(p0, p1);
+                    tsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[i]), ones2, tsum, false);
+                }
+                pf[s] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+            }
+        };
+        // Weights against the reference max m, set by the wave's first tile
+        // and moved (O and the row sum rescaled) only when a lane's sum of
+        // them shows that one could pass 2^16.  A column that its wave's first
+        // tile does not show a key sees none of the later ones either.
+        auto row_max = [&]() {
+            float mt = sc[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mt = fmaxf(mt, sc[r]);
+            return pair_max(mt);
+        };
+        if (t == wave) {
+            m = row_max();
+            if (m == -INFINITY) m = kNoKey;
+        }
+        weights();
+        if (__builtin_amdgcn_ballot_w64(!(tsum <= kWeightCap)) != 0) {
+            const float m_new = fmaxf(m, row_max());
+            const float alpha = __builtin_amdgcn_exp2f((m - m_new) * sl2);
+            lsum *= alpha;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
+            m = m_new;
+            weights();
+        }
+        lsum += tsum;
+        if (more)
+            __builtin_amdgcn_s_waitcnt(WAIT_OLD);  // V(t)
+        else
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (lds_s16x4*)(vb + v_rd(db, 0) + s * 16 * ROWB));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (lds_s16x4*)(vb + v_rd(db, 1) + s * 16 * ROWB));
+                const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+                const bf16x8 av = __builtin_bit_cast(bf16x8, u32x4{l2[0], l2[1], h2[0], h2[1]});
+                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pf[s], oacc[db], 0, 0, 0);
+            }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): V(t) is read
+        if (!more) break;
+        copy(true, vb);
+    }
+
+    // ---- merge of the waves: O rows in LDS (16-byte chunks swizzled by
+    // column), then eight dims of one column per thread
+    lsum = pair_sum(lsum);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int c = db % (NDB / 2) * 8 + r4 * 2 + half;  // 16-byte chunk of the half row
+            *reinterpret_cast<f32x4*>((db < NDB / 2 ? kb : vb) + l32 * ROWB + ((c ^ (l32 % CPR)) << 4)) =
+                f32x4{oacc[db][r4 * 4], oacc[db][r4 * 4 + 1], oacc[db][r4 * 4 + 2], oacc[db][r4 * 4 + 3]};
+        }
+    if (half == 0) {
+        sm.ml[wave][l32][0] = m == kNoKey ? -INFINITY : m;
+        sm.ml[wave][l32][1] = lsum;
+    }
+    __syncthreads();
+    for (int i = tid; i < used * CPR; i += kThreads) {
+        const int col = i / CPR, c = i % CPR;
+        const int j = j0 + col, row = j / R, head = g * R + j % R;
+        float mx = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < W; ++w) mx = fmaxf(mx, sm.ml[w][col][0]);
+        float num[8] = {}, den = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float mw = sm.ml[w][col][0];
+            const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - mx) * sl2);
+            den += f * sm.ml[w][col][1];
+            const char* o = (c < CPR / 2 ? k_st[w] : v_st[w]) + col * ROWB;
+#pragma unroll
+            for (int h2 = 0; h2 < 2; ++h2) {
+                const f32x4 x =
+                    *reinterpret_cast<const f32x4*>(o + (((c % (CPR / 2) * 2 + h2) ^ (col % CPR)) << 4));
+#pragma unroll
+                for (int k = 0; k < 4; ++k) num[h2 * 4 + k] += f * x[k];
+            }
+        }
+        const float inv = 1.0f / den;
+        const u32x4 o = {pack_bf16x2(num[0] * inv, num[1] * inv), pack_bf16x2(num[2] * inv, num[3] * inv),
+                         pack_bf16x2(num[4] * inv, num[5] * inv), pack_bf16x2(num[6] * inv, num[7] * inv)};
+        if ((long)q_row0 + row < 0 || (long)q_row0 + row >= a.lse_rows) continue;
+        *reinterpret_cast<u32x4*>(a.out + ((size_t)(q_row0 + row) * a.n_q_heads + head) * HD + c * 8) = o;
+        if (a.lse && c == 0)
+            a.lse[(size_t)head * a.lse_rows + q_row0 + row] = mx * sl2 * 0.69314718055994531f + logf(den);
+    }
+}
+
+template <int HD, int W>
+hipError_t launch(const AttnArgs& b, unsigned blocks, hipStream_t stream) {
+    hipLaunchKernelGGL((attn_split_kernel<HD, W>), dim3(blocks), dim3(W * 64), 0, stream, b);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attn_split(const AttnArgs& a, int head_dim, int waves, hipStream_t stream) {
+    AttnArgs b = a;
+    b.max_rows = (int)std::min((long)a.max_rows, a.lse_rows);  // no unit has more rows
+    b.n_qt = (int)(((long)b.max_rows * a.ratio + kCols - 1) / kCols);
+    const long blocks = (long)b.n_qt * b.n_units * b.n_kv_heads;
+    if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+    if (head_dim == 128)
+        return waves == 8 ? launch<128, 8>(b, (unsigned)blocks, stream) : launch<128, 4>(b, (unsigned)blocks, stream);
+    return waves == 8 ? launch<64, 8>(b, (unsigned)blocks, stream) : launch<64, 4>(b, (unsigned)blocks, stream);
+}
+
+}  // namespace rc

@@ -13,6 +13,10 @@ namespace {
 // A lane's sum of a tile's weights above this moves the reference max.
 constexpr float kWeightCap = 65536.0f;  // 2^16
 constexpr int kMaxSeg = 1024;
+// Stands for "no visible key" as a reference max where a wave may hold columns
+// that see none of its keys: finite, so that masked logits still weigh
+// exp2(-inf) = 0 against it.
+constexpr float kNoKey = -1e30f;
 // Third dword of a gfx9 buffer resource for raw (unformatted) loads.
 constexpr int kBufferFlags = 0x00020000;
 

@@ -47,10 +47,14 @@ struct AttnArgs {
     const int32_t* cu_kept;
     const int32_t* res_off;  // route-compacted store rows [n_res * Hkv], or NULL
     int max_rows;            // query rows of the longest unit (the grid covers no more)
+    int max_keys;            // prefill: bound on a stream's keys, 0 unknown (chooses the form only)
     const int32_t* plan;     // prefill: work order of the (request, group) pairs
                              // [n_layers][n_units * n_kv_heads], or NULL
 };
 hipError_t launch_attn_mfma(const AttnArgs& a, bool encode, int head_dim, hipStream_t stream);
+// Prefill of small grids: 32 (row, head) columns per block, keys split over
+// its waves (4 or 8); fills n_qt with the column blocks per unit.
+hipError_t launch_attn_split(const AttnArgs& a, int head_dim, int waves, hipStream_t stream);
 // Query rows of one prefill block (32 per row block) for a group size.
 int attend_block_rows(int ratio);
 
