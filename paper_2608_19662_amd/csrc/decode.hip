@@ -18,7 +18,12 @@
 // pipelines (own registers, own LDS buffers, no barriers in the loop): K and
 // V of tile t + 1 are in flight while tile t is computed.  The four partial
 // softmax states are merged in LDS at the end, and a second kernel merges the
-// splits.
+// splits.  64 requests over 32 resources (30% of tokens, 25% of routes) plus
+// 4,096 context rows, 32 / 8 heads, head_dim 128: 306 us a layer, 5.9 TB/s of
+// the 6.2 that a large elementwise copy reaches (325 us while the compiler's
+// waits drained the prefetch; see load_tile).
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -29,10 +34,13 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kTk = 32;  // keys per wave tile
 constexpr int kMaxSeg = 1024;
+// Third dword of a gfx9 buffer resource for raw (unformatted) loads.
+constexpr int kBufferFlags = 0x00020000;
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
+// (addresses held as integers: a plain pointer made from one is a flat access)
+typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 template <int C>
@@ -55,13 +63,11 @@ struct DT {
     static constexpr int WAIT_PREV = (NLOAD & 15) | ((NLOAD >> 4) << 14) | 0x0F70;
 };
 
-template <int HD>
 struct DecSmem {
     int seg_start[kMaxSeg + 1];
     int seg_row[kMaxSeg];
-    int scan[4];  // wave totals of the segment-length scan
-    // per wave: two V tile buffers; reused for the cross-wave merge
-    alignas(16) char v[4][2][DT<HD>::TILEB];
+    int scan[4];       // wave totals of the segment-length scan
+    float ml[4][16][2];  // per wave and head: max, sum (for the merge)
 };
 
 // Chunk swizzle of a V tile row: the 16 rows x 32 bytes that one transpose
@@ -74,12 +80,25 @@ __device__ __forceinline__ int v_mask(int row) {
 __device__ __forceinline__ float xor16_max(float x) { return fmaxf(x, __shfl_xor(x, 16)); }
 __device__ __forceinline__ float xor16_sum(float x) { return x + __shfl_xor(x, 16); }
 
-template <int HD>
+// A wave-uniform 64-bit value, pinned to scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+// BIG: a plane of 4 GiB or more, which a buffer resource cannot address.
+template <int HD, bool BIG>
 __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a) {
     using T = DT<HD>;
-    __shared__ DecSmem<HD> sm;
+    __shared__ DecSmem sm;
+    // Per wave two V tile buffers, in two arrays: the compiler then sees that
+    // the copies in flight into one do not touch the tile being read, and
+    // does not wait for them.  After the loop the first takes the wave's O,
+    // fp32 [16 heads][HD].
+    __shared__ __attribute__((aligned(16))) char v_all0[4][T::TILEB], v_all1[4][T::TILEB];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: a scalar
     const int l16 = lane & 15, grp = lane >> 4;  // MFMA column and row group of this lane
 
     int bid = blockIdx.x;
@@ -156,110 +175,104 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
         }
     }
     if (tid == 0) sm.seg_start[n_seg] = s_vis;
+    // a scalar, so that the loop's branches on what follows from it are, too
+    s_vis = __builtin_amdgcn_readfirstlane(s_vis);
     const int c0 = a.cu_ctx[b];
     const int tc = a.cu_ctx[b + 1] - c0;
     const int n_keys = s_vis + tc;
-    // this split's key range: whole 32-key tiles, the last one possibly partial
+    // This split's key range [s0, s1): its resource rows [g0, g1) of the
+    // stream, 32 keys per tile, then its context rows [x0, x1), so that every
+    // tile has its rows in one buffer.
     int chunk = (n_keys + a.n_splits - 1) / a.n_splits;
     chunk = (chunk + kTk - 1) / kTk * kTk;
     const int s0 = min(split * chunk, n_keys);
     const int s1 = min(s0 + chunk, n_keys);
-    const int n_tiles = (s1 - s0 + kTk - 1) / kTk;
+    const int g0 = min(s0, s_vis), g1 = min(s1, s_vis);
+    const int x0 = max(s0, s_vis) - s_vis, x1 = max(s1, s_vis) - s_vis;
+    const int n_segt = (g1 - g0 + kTk - 1) / kTk;
+    const int n_tiles = n_segt + (x1 - x0 + kTk - 1) / kTk;
     __syncthreads();
 
-    const uint16_t* rk = a.rk + (size_t)g * a.r_gstride * HD;
-    const uint16_t* rv = a.rv + (size_t)g * a.r_gstride * HD;
-    const uint16_t* ck = a.ck + (size_t)g * a.c_rows * HD;
-    const uint16_t* cv = a.cv + (size_t)g * a.c_rows * HD;
-    // Row of stream key p in its buffer (p < s_vis: kept resource rows, else
-    // context rows), clamped into the buffer.  A lane's segment index only
-    // moves forward, since each lane visits its keys in increasing order.
-    auto row_of = [&](int p, int& sidx, int& hi, int& dl) -> size_t {
-        if (p < s_vis) {
-            while (p >= hi && sidx + 1 < n_seg) {
-                ++sidx;
-                hi = sm.seg_start[sidx + 1];
-                dl = sm.seg_row[sidx] - sm.seg_start[sidx];
-            }
-            return min((size_t)(dl + p), (size_t)a.r_rows - 1);
-        }
-        return min((size_t)c0 + (p - s_vis), (size_t)a.c_rows - 1);
-    };
-    const int seg_hi0 = n_seg > 0 ? sm.seg_start[1] : 0;
-    const int seg_dl0 = n_seg > 0 ? sm.seg_row[0] : 0;
-    int ks_i = 0, ks_hi = seg_hi0, ks_dl = seg_dl0;  // walk for this lane's K keys
-    int vs_i = 0, vs_hi = seg_hi0, vs_dl = seg_dl0;  // walk for this lane's V keys
-    int us_i = 0;                                     // wave-uniform walk (fast test)
-    int us_hi = __builtin_amdgcn_readfirstlane(seg_hi0), us_dl = __builtin_amdgcn_readfirstlane(seg_dl0);
+    // Last rows of the two buffers, pinned to scalar registers: selected from
+    // the argument block they become a load and a wait per lookup.
+    const int r_last = __builtin_amdgcn_readfirstlane((int)a.r_rows - 1);
+    const int c_last = __builtin_amdgcn_readfirstlane((int)a.c_rows - 1);
+    // this lane's segment walk (key l32 of each tile), forward only
+    int ls_i = 0, ls_hi = n_seg > 0 ? sm.seg_start[1] : 0, ls_dl = n_seg > 0 ? sm.seg_row[0] : 0;
+    // first stream position (resource rows) or context row of tile t, and its
+    // range's end
+    auto tile_begin = [&](int t) { return t < n_segt ? g0 + t * kTk : x0 + (t - n_segt) * kTk; };
+    auto tile_end = [&](int t) { return t < n_segt ? g1 : x1; };
 
     // ---- loads of one tile.  K: lane holds key kb*16 + l16 of the tile,
     // dims ks*32 + grp*8 + [0, 8), in registers.  V: copy j of the wave moves
     // rows j*RPI + i / CPR of the tile; lane i lands at byte 16 i, i.e.
     // physical chunk i % CPR, which holds logical chunk (i % CPR) ^ v_mask(row).
-    char* vbuf = sm.v[wave][0];
-    u32x4 kreg[2][2][T::NKS];  // [buffer][key block][k-step]
-    auto load_tile = [&](auto buf_tag, int t) {
-        constexpr int buf = decltype(buf_tag)::value;
-        const int tb = s0 + (wave + 4 * t) * kTk;  // first key of the tile
-        // fast tile: all 32 keys consecutive in one buffer (wave-uniform test)
-        bool fast = false;
-        const uint16_t* kb0 = rk;
-        const uint16_t* vb0 = rv;
-        if (tb + kTk <= s1) {
-            if (tb + kTk <= s_vis) {
-                while (tb >= us_hi && us_i + 1 < n_seg) {
-                    ++us_i;
-                    us_hi = __builtin_amdgcn_readfirstlane(sm.seg_start[us_i + 1]);
-                    us_dl = __builtin_amdgcn_readfirstlane(sm.seg_row[us_i]) -
-                            __builtin_amdgcn_readfirstlane(sm.seg_start[us_i]);
-                }
-                const long row0 = (long)us_dl + tb;
-                if (tb + kTk <= us_hi && row0 >= 0 && row0 + kTk <= a.r_rows) {
-                    fast = true;
-                    kb0 = rk + row0 * HD;
-                    vb0 = rv + row0 * HD;
-                }
-            } else if (tb >= s_vis) {
-                const long row0 = (long)c0 + (tb - s_vis);
-                if (row0 + kTk <= a.c_rows) {
-                    fast = true;
-                    kb0 = ck + row0 * HD;
-                    vb0 = cv + row0 * HD;
-                }
-            }
-        }
-        u64x2 ksrc;
-        if (fast) {
+    // Lane k looks up the row of key k (clamped into its buffer) and the loads
+    // fetch row offsets from there: one straight line of 16 loads, whatever
+    // the tile straddles, so that the compiler's waits count them exactly (a
+    // branch per kind of tile made it wait for all loads in flight).
+    char* const v_st0 = v_all0[wave];
+    char* const v_st1 = v_all1[wave];
+    uint32_t v_lane[2];  // byte offset of this lane's chunk within its row, copies 2i and 2i + 1
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) ksrc[kb] = (uint64_t)(kb0 + (kb * 16 + l16) * HD);
+    for (int j = 0; j < 2; ++j)
+        v_lane[j] = (uint32_t)(((lane % T::CPR) ^ v_mask<T::CPR>(j * T::RPI + lane / T::CPR)) << 4);
+    u32x4 kreg[2][2][T::NKS];  // [buffer][key block][k-step]
+    auto load_tile = [&](auto buf_tag, int i) {
+        constexpr int buf = decltype(buf_tag)::value;
+        const int t = wave + 4 * i;
+        const bool seg = t < n_segt;
+        const int p = min(tile_begin(t) + (lane & 31), tile_end(t) - 1);  // past the range: its last key
+        int row;
+        if (seg) {
+            while (p >= ls_hi && ls_i + 1 < n_seg) {
+                ++ls_i;
+                ls_hi = sm.seg_start[ls_i + 1];
+                ls_dl = sm.seg_row[ls_i] - sm.seg_start[ls_i];
+            }
+            row = min(ls_dl + p, r_last);
         } else {
+            row = min(c0 + p, c_last);
+        }
+        row = max(row, 0);
+        const int off = BIG ? row : row * T::ROWB;
+        const uint64_t kp = uniform64((uint64_t)((seg ? a.rk : a.ck) + (size_t)g * (seg ? a.r_gstride : a.c_rows) * HD));
+        const uint64_t vp = uniform64((uint64_t)((seg ? a.rv : a.cv) + (size_t)g * (seg ? a.r_gstride : a.c_rows) * HD));
+        char* dst = buf ? v_st1 : v_st0;
+        if constexpr (BIG) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const int p = min(tb + kb * 16 + l16, s1 - 1);
-                const size_t r = row_of(p, ks_i, ks_hi, ks_dl);
-                ksrc[kb] = (uint64_t)((p < s_vis ? rk : ck) + r * HD);
+                const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(l16 * 4 + kb * 64, off);
+                const uint64_t src = kp + r * T::ROWB + grp * 16;
+#pragma unroll
+                for (int ks = 0; ks < T::NKS; ++ks) kreg[buf][kb][ks] = ((const global_u32x4*)src)[ks * 4];
             }
-        }
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int ks = 0; ks < T::NKS; ++ks)
-                kreg[buf][kb][ks] =
-                    *reinterpret_cast<const u32x4*>((const uint16_t*)ksrc[kb] + ks * 32 + grp * 8);
-        char* dst = vbuf + buf * T::TILEB;
-#pragma unroll
-        for (int j = 0; j < T::NJ; ++j) {
-            const int row = j * T::RPI + lane / T::CPR;
-            const int chunk = (lane % T::CPR) ^ v_mask<T::CPR>(row);
-            const uint16_t* src;
-            if (fast) {
-                src = vb0 + row * HD + chunk * 8;
-            } else {
-                const int p = min(tb + row, s1 - 1);
-                const size_t r = row_of(p, vs_i, vs_hi, vs_dl);
-                src = (p < s_vis ? rv : cv) + r * HD + chunk * 8;
+            for (int j = 0; j < T::NJ; ++j) {
+                const uint64_t r =
+                    (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(lane / T::CPR * 4 + j * T::RPI * 4, off);
+                const uint64_t src = vp + r * T::ROWB + v_lane[j & 1];
+                __builtin_amdgcn_global_load_lds((const uint16_t*)src, (lds_void*)(dst + j * 1024), 16, 0, 0);
             }
-            __builtin_amdgcn_global_load_lds(src, (lds_void*)(dst + j * 1024), 16, 0, 0);
+        } else {
+            const int bytes = __builtin_amdgcn_readfirstlane((int)((seg ? a.r_rows : a.c_rows) * T::ROWB));
+            const __amdgpu_buffer_rsrc_t kr =
+                __builtin_amdgcn_make_buffer_rsrc((void*)kp, (short)0, bytes, kBufferFlags);
+            const __amdgpu_buffer_rsrc_t vr =
+                __builtin_amdgcn_make_buffer_rsrc((void*)vp, (short)0, bytes, kBufferFlags);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                const int o = __builtin_amdgcn_ds_bpermute(l16 * 4 + kb * 64, off) + grp * 16;
+#pragma unroll
+                for (int ks = 0; ks < T::NKS; ++ks)
+                    kreg[buf][kb][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, o + ks * 64, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < T::NJ; ++j) {
+                const int o = __builtin_amdgcn_ds_bpermute(lane / T::CPR * 4 + j * T::RPI * 4, off) + (int)v_lane[j & 1];
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void*)(dst + j * 1024), 16, (int)o, 0, 0, 0);
+            }
         }
     };
 
@@ -282,9 +295,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
 #pragma unroll
     for (int db = 0; db < T::NDB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    auto compute = [&](auto buf_tag, int t) {
+    auto compute = [&](auto buf_tag, int i) {
         constexpr int buf = decltype(buf_tag)::value;
-        const int tb = s0 + (wave + 4 * t) * kTk;
+        const int t = wave + 4 * i;
+        const int n_in = tile_end(t) - tile_begin(t);  // keys of the tile in its range (32 or more: all)
         f32x4 sacc[2];
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
@@ -294,13 +308,13 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
                 sacc[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                     __builtin_bit_cast(bf16x8_t, kreg[buf][kb][ks]), qf[ks], sacc[kb], 0, 0, 0);
         }
-        // keys past the range end (last tile of the range only)
-        if (tb + kTk > s1) {
+        // keys past the range's end (its last tile only)
+        if (n_in < kTk) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (tb + kb * 16 + grp * 4 + r >= s1) sacc[kb][r] = -INFINITY;
+                    if (kb * 16 + grp * 4 + r >= n_in) sacc[kb][r] = -INFINITY;
         }
         float mt = fmaxf(fmaxf(fmaxf(sacc[0][0], sacc[0][1]), fmaxf(sacc[0][2], sacc[0][3])),
                          fmaxf(fmaxf(sacc[1][0], sacc[1][1]), fmaxf(sacc[1][2], sacc[1][3])));
@@ -328,7 +342,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
                 lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones2, lsum, false);
             }
         const bf16x8_t pf = __builtin_bit_cast(bf16x8_t, u32x4{w[0], w[1], w[2], w[3]});
-        const char* st = vbuf + buf * T::TILEB;
+        const char* st = buf ? v_st1 : v_st0;
 #pragma unroll
         for (int db = 0; db < T::NDB; ++db) {
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(st + tr_off(db, 0)));
@@ -341,24 +355,28 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
 
     // This wave's tiles are wave, wave + 4, ... of the range; the loads of
     // the next one are in flight while one is computed.  Only this wave
-    // reads its V buffers, so waiting for its own copies is enough.
+    // reads its V buffers, so waiting for its own copies is enough.  (Each
+    // exit has its own copy of the computation, so that inside the loop the
+    // compiler's waits count the newer tile's loads as these do.)
     const int my_tiles = n_tiles > wave ? (n_tiles - wave + 3) / 4 : 0;
-    if (my_tiles > 0) load_tile(Tag<0>{}, 0);
-    for (int t = 0; t < my_tiles; t += 2) {
-        if (t + 1 < my_tiles) {
+    if (my_tiles > 0) {
+        load_tile(Tag<0>{}, 0);
+        for (int t = 0;; t += 2) {
+            if (t + 1 >= my_tiles) {
+                __builtin_amdgcn_s_waitcnt(0x0F70);
+                compute(Tag<0>{}, t);
+                break;
+            }
             load_tile(Tag<1>{}, t + 1);
             __builtin_amdgcn_s_waitcnt(T::WAIT_PREV);
-        } else {
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-        }
-        compute(Tag<0>{}, t);
-        if (t + 1 < my_tiles) {
-            if (t + 2 < my_tiles) {
-                load_tile(Tag<0>{}, t + 2);
-                __builtin_amdgcn_s_waitcnt(T::WAIT_PREV);
-            } else {
+            compute(Tag<0>{}, t);
+            if (t + 2 >= my_tiles) {
                 __builtin_amdgcn_s_waitcnt(0x0F70);
+                compute(Tag<1>{}, t + 1);
+                break;
             }
+            load_tile(Tag<0>{}, t + 2);
+            __builtin_amdgcn_s_waitcnt(T::WAIT_PREV);
             compute(Tag<1>{}, t + 1);
         }
     }
@@ -366,30 +384,30 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
     // ---- merge: the four row groups of a head hold disjoint dims of O^T and
     // parts of its row sum; then the four waves, through LDS.
     lsum = pair_sum(xor16_sum(lsum));
-    __syncthreads();  // every wave is done with its V buffers
-    float* mo = reinterpret_cast<float*>(&sm.v[0][0][0]);  // [wave][16 heads][HD]
-    float* mml = mo + 4 * 16 * HD;                           // [wave][16 heads][2]
+    static_assert(16 * HD * 4 == T::TILEB, "a wave's O fills a V buffer");
+    // (16-byte chunks swizzled by head; only this wave touched its buffers, so
+    // no barrier before the writes)
 #pragma unroll
     for (int db = 0; db < T::NDB; ++db)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) mo[(wave * 16 + l16) * HD + db * 16 + grp * 4 + r] = oacc[db][r];
+        *reinterpret_cast<f32x4*>(v_st0 + (l16 * (HD / 4) + ((db * 4 + grp) ^ l16)) * 16) = oacc[db];
     if (grp == 0) {
-        mml[(wave * 16 + l16) * 2 + 0] = m;
-        mml[(wave * 16 + l16) * 2 + 1] = lsum;
+        sm.ml[wave][l16][0] = m;
+        sm.ml[wave][l16][1] = lsum;
     }
     __syncthreads();
     for (int idx = tid; idx < R * HD; idx += kThreads) {
         const int h = idx / HD, d = idx % HD;
         float mx = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mx = fmaxf(mx, mml[(w * 16 + h) * 2]);
+        for (int w = 0; w < 4; ++w) mx = fmaxf(mx, sm.ml[w][h][0]);
         float num = 0.f, den = 0.f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const float mw = mml[(w * 16 + h) * 2];
+            const float mw = sm.ml[w][h][0];
             const float sc = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - mx);
-            num += sc * mo[(w * 16 + h) * HD + d];
-            den += sc * mml[(w * 16 + h) * 2 + 1];
+            const char* o = v_all0[w] + (h * (HD / 4) + ((d >> 2) ^ h)) * 16 + (d & 3) * 4;
+            num += sc * *reinterpret_cast<const float*>(o);
+            den += sc * sm.ml[w][h][1];
         }
         const size_t slot = ((size_t)b * a.n_q_heads + g * R + h) * a.n_splits + split;
         a.ws_o[slot * HD + d] = num;
@@ -460,7 +478,11 @@ __global__ __launch_bounds__(HD) void combine_kernel(const DecodeArgs a) {
 template <int HD>
 hipError_t launch_dec(const DecodeArgs& a, hipStream_t s) {
     const long blocks = (long)a.n_req * a.n_kv_heads * a.n_splits;
-    hipLaunchKernelGGL((decode_kernel<HD>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+    const bool big = (unsigned long)std::max(a.r_rows, a.c_rows) * HD * 2 >= (1UL << 32);
+    if (big)
+        hipLaunchKernelGGL((decode_kernel<HD, true>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((decode_kernel<HD, false>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((combine_kernel<HD>), dim3((unsigned)(a.n_req * a.n_q_heads)), dim3(HD), 0, s, a);

@@ -1,0 +1,43 @@
+"""GPU: decode where its addressing and its split of the key stream change:
+KV planes of 4 GiB and more (addressed by pointer, smaller ones through a
+buffer resource), and ranges that end inside, at and between the resource and
+context rows of short and long streams."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import DEV, Routes, i32
+from paper_2608_19662_amd import recache as rc
+from test_gpu_parity import print_case, run_attend_case, small_attend
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_plane_of_4_gib(d):
+    """The same rows at the end of a plane past 4 GiB and in a small one: the
+    same bits."""
+    print_case("decode 4 GiB plane", d)
+    w = small_attend(141, 1, 4, 4, 1, d, "bf16", [1], [333], L=1, mask_p=2.0)
+    rt = Routes(w)
+    q, ck, cv, rk, rv = w.layer_tensors(0, DEV)
+    mk = rt.max_kv(0)
+    ws = rt.workspace(mk)
+    out, lse = rt.attend(q, ck, cv, rk, rv, 0, workspace=ws, max_kv=mk)
+    rows = (1 << 32) // (2 * d) + 5
+    big_k = torch.empty(1, rows, d, dtype=ck.dtype, device=DEV)
+    big_v = torch.empty_like(big_k)
+    big_k[:, -333:], big_v[:, -333:] = ck, cv
+    rt.cu_ctx = i32([rows - 333, rows])
+    big, big_lse = rt.attend(q, big_k, big_v, rk, rv, 0, workspace=ws, max_kv=mk)
+    torch.cuda.synchronize()
+    assert torch.equal(out, big) and torch.equal(lse, big_lse)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (12, 4, 64)])
+@pytest.mark.parametrize("ctx", [[1, 31, 32], [33, 127, 128], [129, 4000, 9000]])
+def test_decode_ranges(Hq, Hkv, d, ctx):
+    print_case("decode ranges", Hq, Hkv, d, ctx)
+    w = small_attend(142 + ctx[0], 3, 6, Hq, Hkv, d, "bf16", [1, 1, 1], ctx, L=2, max_len=500)
+    for layer in range(2):
+        run_attend_case(w, layer)
