@@ -53,7 +53,7 @@ template <int HD>
 struct F32Smem {
     int seg_start[kMaxSeg + 1];
     int seg_row[kMaxSeg];
-    int scan[kWaves];
+    int scan[2 * kWaves];
     float ml[kWaves][kCols][2];
     // per wave: the V tile [32 keys][HD]; before the loop the cos / sin table,
     // after it the wave's O [32 columns][HD]
@@ -176,34 +176,12 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args
         if constexpr (ENCODE) {
             s_vis = a.p_len;
             if (tid == 0) sm.seg_start[0] = 0, sm.seg_start[1] = s_vis, sm.seg_row[0] = 0;
+            __syncthreads();
         } else {
             if (seg0 > 0) __syncthreads();  // every wave is done with the previous pass's table
-            constexpr int SPT = kMaxSeg / kThreads;
-            int lens[SPT], part = 0;
-#pragma unroll
-            for (int i = 0; i < SPT; ++i) {
-                const int s = tid * SPT + i;
-                lens[i] = 0;
-                if (s < ns) {
-                    const int r = a.route_res[r0 + seg0 + s];
-                    const int k0 = a.cu_kept[r];
-                    const int beg = a.res_off ? a.res_off[(size_t)r * a.n_kv_heads + g] : k0;
-                    // rows past the end of the plane are not visited
-                    lens[i] = (int)max(0L, min((long)a.cu_kept[r + 1] - k0, a.k_rows - beg));
-                    sm.seg_row[s] = beg;
-                }
-                part += lens[i];
-            }
-            int run = block4_exclusive_scan(part, sm.scan, &s_vis);
-#pragma unroll
-            for (int i = 0; i < SPT; ++i) {
-                const int s = tid * SPT + i;
-                if (s < ns) sm.seg_start[s] = run;
-                run += lens[i];
-            }
-            if (tid == 0) sm.seg_start[ns] = s_vis;
+            s_vis = segment_table<kWaves, true>(a.route_res + r0 + seg0, ns, a.cu_kept, a.res_off, a.n_kv_heads, g,
+                                                a.k_rows, sm.seg_start, sm.seg_row, sm.scan);
         }
-        __syncthreads();
         const int n_keys = s_vis + (last_pass ? max(0, block_last + 1) : 0);
         const int n_tiles = (n_keys + kKeys - 1) / kKeys;
         // stream positions up to these are visible to the column / to all columns

@@ -107,7 +107,7 @@ template <bool ENCODE, int NW>
 struct Smem {
     int seg_start[ENCODE ? 2 : kMaxSeg + 1];
     int seg_row[ENCODE ? 2 : kMaxSeg];
-    int scan[NW];  // wave totals of the segment-length scan
+    int scan[2 * NW];  // of the segment-length scan
 };
 
 __device__ __forceinline__ void wait_vm0() {
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
 
     if constexpr (!ENCODE) {
         // Visible segments of this (request, layer, group): kept rows of the
-        // routed resources, request order.  Exclusive scan of their lengths.
+        // routed resources, request order.
         const size_t e = ((size_t)unit * a.n_layers + a.layer) * a.n_kv_heads + g;
         const int r0 = a.route_off[e];
         n_seg = a.route_off[e + 1] - r0;
@@ -204,30 +204,8 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attn_mfma_kernel(const AttnAr
                 poison_rows<HD>(a, head, 1, q_row0, rb * 32, min(rb * 32 + 32, q_lim), lane, 64);
             return;
         }
-        constexpr int SPT = kMaxSeg / kThreads;  // segments per thread
-        int part = 0;
-        int lens[SPT];
-#pragma unroll
-        for (int i = 0; i < SPT; ++i) {
-            const int s = tid * SPT + i;
-            lens[i] = 0;
-            if (s < n_seg) {
-                const int r = a.route_res[r0 + s];
-                const int k0 = a.cu_kept[r];
-                lens[i] = a.cu_kept[r + 1] - k0;
-                sm.seg_row[s] = a.res_off ? a.res_off[(size_t)r * a.n_kv_heads + g] : k0;
-            }
-            part += lens[i];
-        }
-        int run = block_exclusive_scan<NW>(part, sm.scan, &s_vis);
-#pragma unroll
-        for (int i = 0; i < SPT; ++i) {
-            const int s = tid * SPT + i;
-            if (s < n_seg) sm.seg_start[s] = run;
-            run += lens[i];
-        }
-        if (tid == 0) sm.seg_start[n_seg] = s_vis;
-        __syncthreads();
+        s_vis = segment_table<NW, false>(a.route_res + r0, n_seg, a.cu_kept, a.res_off, a.n_kv_heads, g, 0,
+                                         sm.seg_start, sm.seg_row, sm.scan);
     }
     off = s_vis + tc - q_len;
     stream = s_vis + tc;

@@ -36,7 +36,7 @@ template <int W>
 struct SplitSmem {
     int seg_start[kMaxSeg + 1];
     int seg_row[kMaxSeg];
-    int scan[W];
+    int scan[2 * W];
     float ml[W][kCols][2];
 };
 
@@ -109,34 +109,8 @@ __global__ __launch_bounds__(W * 64, 2) void attn_split_kernel(const AttnArgs a)
             poison_rows<HD>(a, g * R + j % R, 1, q_row0, j / R, j / R + 1, lane, 64);
         return;
     }
-    int s_vis;
-    {
-        constexpr int SPT = kMaxSeg / kThreads;
-        int lens[SPT], part = 0;
-#pragma unroll
-        for (int i = 0; i < SPT; ++i) {
-            const int s = tid * SPT + i;
-            lens[i] = 0;
-            if (s < n_seg) {
-                const int r = a.route_res[r0 + s];
-                const int k0 = a.cu_kept[r];
-                lens[i] = a.cu_kept[r + 1] - k0;
-                sm.seg_row[s] = a.res_off ? a.res_off[(size_t)r * a.n_kv_heads + g] : k0;
-            }
-            part += lens[i];
-        }
-        int run = block_exclusive_scan<W>(part, sm.scan, &s_vis);
-#pragma unroll
-        for (int i = 0; i < SPT; ++i) {
-            const int s = tid * SPT + i;
-            if (s < n_seg) sm.seg_start[s] = run;
-            run += lens[i];
-        }
-        if (tid == 0) sm.seg_start[n_seg] = s_vis;
-        // a scalar, so that what is chosen by it below is seen to be uniform
-        s_vis = __builtin_amdgcn_readfirstlane(s_vis);
-    }
-    __syncthreads();
+    const int s_vis = segment_table<W, false>(a.route_res + r0, n_seg, a.cu_kept, a.res_off, a.n_kv_heads, g, 0,
+                                              sm.seg_start, sm.seg_row, sm.scan);
     // Tiles: the segment rows' 32 at a time, then the causal rows', so that
     // every tile has its rows in one plane.
     const int off = tc - q_len;                          // a column sees causal rows <= off + row

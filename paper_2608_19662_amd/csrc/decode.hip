@@ -66,7 +66,7 @@ struct DT {
 struct DecSmem {
     int seg_start[kMaxSeg + 1];
     int seg_row[kMaxSeg];
-    int scan[4];       // wave totals of the segment-length scan
+    int scan[8];  // of the segment-length scan
     float ml[4][16][2];  // per wave and head: max, sum (for the merge)
 };
 
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
     }
 
     // ---- visible segments of this (request, layer, group): kept rows of the
-    // routed resources, request order.  Exclusive scan of their lengths.
+    // routed resources, request order.
     const size_t e = ((size_t)b * a.n_layers + a.layer) * a.n_kv_heads + g;
     const int r0 = a.route_off[e];
     const int n_seg = a.route_off[e + 1] - r0;
@@ -151,32 +151,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
         }
         return;
     }
-    int lens[4], part = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int s = tid * 4 + i;
-        lens[i] = 0;
-        if (s < n_seg) {
-            const int r = a.route_res[r0 + s];
-            const int k0 = a.cu_kept[r];
-            lens[i] = a.cu_kept[r + 1] - k0;
-            sm.seg_row[s] = a.res_off ? a.res_off[(size_t)r * a.n_kv_heads + g] : k0;
-        }
-        part += lens[i];
-    }
-    int s_vis;
-    {
-        int run = block4_exclusive_scan(part, sm.scan, &s_vis);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int s = tid * 4 + i;
-            if (s < n_seg) sm.seg_start[s] = run;
-            run += lens[i];
-        }
-    }
-    if (tid == 0) sm.seg_start[n_seg] = s_vis;
-    // a scalar, so that the loop's branches on what follows from it are, too
-    s_vis = __builtin_amdgcn_readfirstlane(s_vis);
+    const int s_vis = segment_table<4, false>(a.route_res + r0, n_seg, a.cu_kept, a.res_off, a.n_kv_heads, g, 0,
+                                              sm.seg_start, sm.seg_row, sm.scan);
     const int c0 = a.cu_ctx[b];
     const int tc = a.cu_ctx[b + 1] - c0;
     const int n_keys = s_vis + tc;
@@ -191,7 +167,6 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
     const int x0 = max(s0, s_vis) - s_vis, x1 = max(s1, s_vis) - s_vis;
     const int n_segt = (g1 - g0 + kTk - 1) / kTk;
     const int n_tiles = n_segt + (x1 - x0 + kTk - 1) / kTk;
-    __syncthreads();
 
     // Last rows of the two buffers, pinned to scalar registers: selected from
     // the argument block they become a load and a wait per lookup.
