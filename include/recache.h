@@ -245,7 +245,8 @@ int recache_store_routes(int dtype, int layer, int n_layers, int n_res, const in
  * passage of the paper: decode (Fig. 2's final mask with one query per
  * request) splits each (request, group) key stream into chunks whose partial
  * outputs and log-sum-exps are merged afterwards; the workspace holds those
- * partials, fp32, n_req * n_q_heads * splits * (head_dim + 2) values.
+ * partials, fp32, n_req * n_q_heads * splits * (head_dim + 2) values (and is
+ * enough for any smaller n_req at the same max_kv).
  * max_kv is an upper bound on the keys a (request, group) can see in one layer
  * (route tokens + context), used only to choose the split count (and by
  * prefill the form of its blocks); 0 means "use max_ctx" (prefill: unknown).  Returns 0 for invalid sizes.  Pure host arithmetic.

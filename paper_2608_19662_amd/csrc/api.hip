@@ -381,7 +381,10 @@ size_t recache_attend_workspace_bytes(int n_req, int max_q, int max_ctx, int max
                                       int n_q_heads, int n_kv_heads, int head_dim) {
     if (n_req <= 0 || max_q != 1 || n_q_heads <= 0 || n_kv_heads <= 0 || head_dim <= 0) return 0;
     const int kv = max_kv > 0 ? max_kv : max_ctx;
-    return decode_workspace_bytes(n_req, n_q_heads, head_dim, decode_splits(n_req, n_kv_heads, kv));
+    if (n_q_heads < n_kv_heads)
+        return decode_workspace_bytes(n_req, n_q_heads, head_dim, decode_splits(n_req, n_kv_heads, kv));
+    return std::max(decode_workspace_bytes(n_req, n_q_heads, head_dim, decode_splits(n_req, n_kv_heads, kv)),
+                    decode_workspace_bytes(1, (int)decode_slots(n_req, n_q_heads, n_kv_heads, kv), head_dim, 1));
 }
 
 }  // extern "C"

@@ -157,6 +157,9 @@ struct DecodeArgs {
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 size_t decode_workspace_bytes(int n_req, int n_q_heads, int head_dim, int n_splits);
 int decode_splits(int n_req, int n_kv_heads, int max_kv);
+// Partial slots for a batch of n_req requests or any smaller one (a program
+// that sizes its workspace for its largest batch keeps it for the others).
+long decode_slots(int n_req, int n_q_heads, int n_kv_heads, int max_kv);
 
 // Work order of the attend kernels (plan.hip): per layer, the pairs
 // b * n_kv_heads + g sorted by their work, longest first, dealt in snake order
