@@ -97,7 +97,7 @@ def version() -> int:
 
 
 def _call(name, *args):
-    rc = getattr(lib(), name)(*args)
+    rc = getattr(_lib or lib(), name)(*args)
     if rc != OK:
         raise RecacheError(rc, "%s: %s" % (name, last_error()))
     return rc
@@ -105,13 +105,26 @@ def _call(name, *args):
 
 # ------------------------------------------------------------- marshalling
 
+# These run some twenty times per call, in front of kernels of a few
+# microseconds: no imports, generators or tuples are made in them.
+
+def _torch():
+    """torch, with the dtypes the checks compare against, bound on first use."""
+    global torch, _I32, _U8
+    import torch
+
+    _I32, _U8 = (torch.int32,), (torch.uint8,)
+    return torch
+
+
+torch = _I32 = _U8 = None
+
+
 def _dev(t, name, dtypes=None):
     """Device pointer of a contiguous CUDA tensor (None -> NULL)."""
     if t is None:
         return None
-    import torch
-
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, (torch or _torch()).Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA tensor" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
@@ -121,32 +134,35 @@ def _dev(t, name, dtypes=None):
 
 
 def _dtype_code(t):
-    import torch
-
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
+    dt = t.dtype
+    if dt is (torch or _torch()).bfloat16:
         return BF16
-    raise TypeError("floating tensors must be float32 or bfloat16, got %s" % t.dtype)
+    if dt is torch.float32:
+        return F32
+    raise TypeError("floating tensors must be float32 or bfloat16, got %s" % dt)
 
 
 def _stream(stream):
-    import torch
-
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # The handle of torch.cuda.current_stream(), without the Stream object
+        # and the environment lookups of its device query.
+        c = (torch or _torch())._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _i32():
-    import torch
+    return _I32 or (_torch() and _I32)
 
-    return (torch.int32,)
+
+def _u8():
+    return _U8 or (_torch() and _U8)
 
 
 def _same(ref, *ts):
+    dt = ref.dtype
     for t in ts:
-        if t is not None and t.dtype != ref.dtype:
+        if t is not None and t.dtype != dt:
             raise TypeError("all floating tensors of a call share one dtype")
 
 
@@ -154,15 +170,13 @@ def _shape(t, name, *dims):
     """Raise unless tensor t (if given) has exactly the shape dims.  Checked
     before any pointer is taken: a buffer smaller than the sizes passed to the
     library would turn into a GPU access outside it."""
-    if t is None:
-        return
-    if tuple(t.shape) != tuple(int(x) for x in dims):
+    if t is not None and t.shape != dims:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(dims)))
 
 
 def _numel(t, name, n):
     """Raise unless tensor t has exactly n elements (1-d index arrays)."""
-    if t is not None and (t.dim() != 1 or t.numel() != int(n)):
+    if t is not None and (t.dim() != 1 or t.numel() != n):
         raise ValueError("%s must be 1-d with %d elements, has shape %s"
                          % (name, int(n), tuple(t.shape)))
 
@@ -277,8 +291,6 @@ def prune_gather(k_cache, v_cache, cu_len, cu_kept, kept_idx, k_kept, v_kept, st
 def build_routes(req_res_off, req_res, route_mask, cu_kept, route_off, route_res, route_tokens,
                  stream=None):
     """Route CSR for every (request, layer, KV group); route_mask is [n_res][L][G] uint8."""
-    import torch
-
     n_res, L, G = route_mask.shape
     n_req = req_res_off.numel() - 1
     E = n_req * L * G
@@ -288,7 +300,7 @@ def build_routes(req_res_off, req_res, route_mask, cu_kept, route_off, route_res
     _at_least(route_res, "route_res", req_res.numel() * L * G)
     _call("recache_build_routes", req_res_off.numel() - 1, _dev(req_res_off, "req_res_off", _i32()),
           _dev(req_res, "req_res", _i32()), req_res.numel(), n_res, L, G,
-          _dev(route_mask, "route_mask", (torch.uint8,)), _dev(cu_kept, "cu_kept", _i32()),
+          _dev(route_mask, "route_mask", _u8()), _dev(cu_kept, "cu_kept", _i32()),
           _dev(route_off, "route_off", _i32()), _dev(route_res, "route_res", _i32()),
           _dev(route_tokens, "route_tokens", _i32()), _stream(stream))
 
@@ -296,15 +308,13 @@ def build_routes(req_res_off, req_res, route_mask, cu_kept, route_off, route_res
 def route_store_offsets(route_mask, cu_kept, store_off, total_kept: int | None = None,
                         stream=None):
     """Row tables of a route-compacted store: store_off is int32 [L][n_res * G + 1]."""
-    import torch
-
     n_res, L, G = route_mask.shape
     _numel(cu_kept, "cu_kept", n_res + 1)
     _shape(store_off, "store_off", L, n_res * G + 1)
     if total_kept is None:
         total_kept = _total(cu_kept)
     _call("recache_route_store_offsets", n_res, L, G, int(total_kept),
-          _dev(route_mask, "route_mask", (torch.uint8,)), _dev(cu_kept, "cu_kept", _i32()),
+          _dev(route_mask, "route_mask", _u8()), _dev(cu_kept, "cu_kept", _i32()),
           _dev(store_off, "store_off", _i32()), _stream(stream))
 
 
