@@ -12,8 +12,8 @@
 // in alternating direction, evens both out.
 //
 // One block per layer: the work of every pair (in key tiles, by the cost
-// model of the attention kernels), a bitonic sort of (work, pair) keys in
-// LDS, then the dealt order.  Keys are unique (ties fall to the lower pair
+// model of the attention kernels), the (work, pair) keys ranked by counting
+// or, beyond 1024 pairs, in a bitonic sort in LDS, then the dealt order.  Keys are unique (ties fall to the lower pair
 // index), so the order is deterministic.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -23,6 +23,7 @@ namespace rc {
 namespace {
 
 constexpr int kPlanThreads = 1024;
+constexpr int kRankPairs = 1024;  // up to this many pairs are ranked by counting
 
 __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArgs a) {
     __shared__ uint64_t key[kMaxPlanPairs];
@@ -56,6 +57,51 @@ __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArg
         key[i] = k;
     }
     __syncthreads();
+    int32_t* out = a.plan + (size_t)layer * n;
+    // Deal: sorted position k goes to grid row k / G, position k % G in even
+    // rows and G - 1 - k % G in odd rows.
+    auto deal = [&](int k, uint64_t key_k) {
+        const int row = k / G, c = k % G;
+        out[row * G + ((row & 1) ? G - 1 - c : c)] = (int)(0xffffffffu - (uint32_t)(key_k & 0xffffffffu));
+    };
+    if (np2 <= kRankPairs) {
+        // Few pairs, one per thread: each wave ranks its 64 keys among
+        // themselves (keys are unique) and stores them in that order; a key's
+        // position is its rank there plus the number of larger keys in every
+        // other wave's run, by binary search (512 pairs of 36 layers: 11.4 us;
+        // in the sort below, a barrier per stage: 13.2).
+        const int i = threadIdx.x, wave = i >> 6, n_runs = (np2 + 63) / 64;
+        const uint64_t mine = i < np2 ? key[i] : 0;
+        const int lo32 = (int)(uint32_t)mine, hi32 = (int)(uint32_t)(mine >> 32);
+        int pos = 0;
+#pragma unroll 8
+        for (int k = 0; k < 64; ++k) {
+            const uint64_t other = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi32, k) << 32) |
+                                   (uint32_t)__builtin_amdgcn_readlane(lo32, k);
+            pos += other > mine;
+        }
+        if (i < n) key[kPlanThreads + wave * 64 + pos] = mine;  // (padding keys are 0, the smallest)
+        __syncthreads();
+        if (i < n) {
+            int at[kRankPairs / 64] = {};  // larger keys in each run
+#pragma unroll
+            for (int step = 32; step >= 1; step >>= 1)
+#pragma unroll
+                for (int r = 0; r < kRankPairs / 64; ++r)
+                    if (r < n_runs && at[r] + step <= min(64, n - r * 64) &&
+                        key[kPlanThreads + r * 64 + at[r] + step - 1] > mine)
+                        at[r] += step;
+#pragma unroll
+            for (int r = 0; r < kRankPairs / 64; ++r) {
+                if (r >= n_runs || r == wave) continue;
+                // the steps reach 63 of a run's 64 keys
+                if (at[r] == 63 && n - r * 64 >= 64 && key[kPlanThreads + r * 64 + 63] > mine) ++at[r];
+                pos += at[r];
+            }
+            deal(pos, mine);
+        }
+        return;
+    }
     // bitonic sort, descending
     for (int size = 2; size <= np2; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
@@ -75,14 +121,7 @@ __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArg
             __syncthreads();
         }
     }
-    // deal: sorted position k goes to grid row k / G, position k % G in even
-    // rows and G - 1 - k % G in odd rows
-    int32_t* out = a.plan + (size_t)layer * n;
-    for (int k = threadIdx.x; k < n; k += kPlanThreads) {
-        const int pair = (int)(0xffffffffu - (uint32_t)(key[k] & 0xffffffffu));
-        const int row = k / G, c = k % G;
-        out[row * G + ((row & 1) ? G - 1 - c : c)] = pair;
-    }
+    for (int k = threadIdx.x; k < n; k += kPlanThreads) deal(k, key[k]);
 }
 
 }  // namespace
