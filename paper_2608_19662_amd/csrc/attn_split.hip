@@ -40,6 +40,28 @@ struct SplitSmem {
     float ml[W][kCols][2];
 };
 
+// Reads a K tile's fragments from LDS and waits for them.
+template <int N>
+__device__ __forceinline__ void read_k(const uint32_t* addr, u32x4* f) {
+    static_assert(N == 4 || N == 8, "head_dim 64 or 128");
+    if constexpr (N == 8)
+        asm volatile(
+            "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+            "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7])
+            : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]), "v"(addr[4]), "v"(addr[5]), "v"(addr[6]),
+              "v"(addr[7])
+            : "memory");
+    else
+        asm volatile(
+            "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3])
+            : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3])
+            : "memory");
+}
+
 template <int HD, int W>
 __global__ __launch_bounds__(W * 64, 2) void attn_split_kernel(const AttnArgs a) {
     constexpr int kThreads = W * 64;
@@ -201,8 +223,6 @@ __global__ __launch_bounds__(W * 64, 2) void attn_split_kernel(const AttnArgs a)
         }
     };
 
-    // K as the A operand: key l32, chunk 2t + half (t moves chunk bits 1..3)
-    const uint32_t k_rd0 = swz<HD>(l32, half);
     // V^T transpose-read offset (see attn_mfma.hip): rows s*16 + w*8 + half*4
     // + [0, 4), the keys that P^T holds in slots w*4 + [0, 4) of step s
     uint32_t v_rd0;
@@ -231,6 +251,10 @@ __global__ __launch_bounds__(W * 64, 2) void attn_split_kernel(const AttnArgs a)
     static_assert(NJ < 16, "vmcnt(NJ) fits the low counter bits");
     char* kb = k_st[wave];
     char* vb = v_st[wave];
+    // K as the A operand: key l32, chunk 2t + half (t moves chunk bits 1..3)
+    uint32_t k_addr[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) k_addr[i] = (uint32_t)(uintptr_t)(lds_void*)kb + (swz<HD>(l32, half) ^ (i << 5));
     if (wave < n_tiles) {
         set_tile(wave);
         copy(false, kb);
@@ -241,13 +265,13 @@ __global__ __launch_bounds__(W * 64, 2) void attn_split_kernel(const AttnArgs a)
     for (int t = wave; wave < n_tiles; t += W) {
         const bool more = t + W < n_tiles;
         __builtin_amdgcn_s_waitcnt(WAIT_OLD);  // K(t)
+        // (The compiler would wait here for the V copies in flight as well.)
+        u32x4 kf[NT];
+        read_k<NT>(k_addr, kf);
         f32x16 sc = {};
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const bf16x8 av = *reinterpret_cast<const bf16x8*>(kb + (k_rd0 ^ (i << 5)));
-            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qf[i], sc, 0, 0, 0);
-        }
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K(t) is read
+        for (int i = 0; i < NT; ++i)
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[i]), qf[i], sc, 0, 0, 0);
         if (more) {
             set_tile(t + W);
             copy(false, kb);
