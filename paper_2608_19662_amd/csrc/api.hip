@@ -506,6 +506,7 @@ int recache_attend_cached(int dtype, int layer, int n_layers, int n_req, const i
         a.ck = static_cast<const uint16_t*>(ctx_k);
         a.cv = static_cast<const uint16_t*>(ctx_v);
         a.c_rows = ctx_rows;
+        a.max_ctx_rows = (long)n_req * max_ctx;
         a.cu_q = cu_q;
         a.cu_ctx = cu_ctx;
         a.layer = layer;

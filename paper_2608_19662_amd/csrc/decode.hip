@@ -19,9 +19,10 @@
 // V of tile t + 1 are in flight while tile t is computed.  The four partial
 // softmax states are merged in LDS at the end, and a second kernel merges the
 // splits.  64 requests over 32 resources (30% of tokens, 25% of routes) plus
-// 4,096 context rows, 32 / 8 heads, head_dim 128: 306 us a layer, 5.9 TB/s of
-// the 6.2 that a large elementwise copy reaches (325 us while the compiler's
-// waits drained the prefetch; see load_tile).
+// 4,096 context rows, 32 / 8 heads, head_dim 128: 283 us a layer, 6.4 TB/s; a
+// large elementwise copy reaches 6.2 (325 us while the compiler's waits
+// drained the prefetch, see load_tile; 306 with the context through the
+// caches).
 #include <algorithm>
 
 #include "common.hpp"
@@ -86,8 +87,10 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
            (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
-// BIG: a plane of 4 GiB or more, which a buffer resource cannot address.
-template <int HD, bool BIG>
+// BIG: a plane of 4 GiB or more, which a buffer resource cannot address.  NT:
+// context rows are loaded with the non-temporal hint (no request reads
+// another's); resource rows never are, since requests share them.
+template <int HD, bool BIG, bool NT>
 __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a) {
     using T = DT<HD>;
     __shared__ DecSmem sm;
@@ -194,8 +197,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
     for (int j = 0; j < 2; ++j)
         v_lane[j] = (uint32_t)(((lane % T::CPR) ^ v_mask<T::CPR>(j * T::RPI + lane / T::CPR)) << 4);
     u32x4 kreg[2][2][T::NKS];  // [buffer][key block][k-step]
-    auto load_tile = [&](auto buf_tag, int i) {
-        constexpr int buf = decltype(buf_tag)::value;
+    auto load_tile = [&](auto buf_tag, auto aux_tag, int i) {
+        constexpr int buf = decltype(buf_tag)::value, AUX = decltype(aux_tag)::value;
         const int t = wave + 4 * i;
         const bool seg = t < n_segt;
         const int p = min(tile_begin(t) + (lane & 31), tile_end(t) - 1);  // past the range: its last key
@@ -241,12 +244,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
                 const int o = __builtin_amdgcn_ds_bpermute(l16 * 4 + kb * 64, off) + grp * 16;
 #pragma unroll
                 for (int ks = 0; ks < T::NKS; ++ks)
-                    kreg[buf][kb][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, o + ks * 64, 0, 0);
+                    kreg[buf][kb][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, o + ks * 64, 0, AUX);
             }
 #pragma unroll
             for (int j = 0; j < T::NJ; ++j) {
                 const int o = __builtin_amdgcn_ds_bpermute(lane / T::CPR * 4 + j * T::RPI * 4, off) + (int)v_lane[j & 1];
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void*)(dst + j * 1024), 16, (int)o, 0, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void*)(dst + j * 1024), 16, (int)o, 0, 0, AUX);
             }
         }
     };
@@ -332,29 +335,39 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
     // the next one are in flight while one is computed.  Only this wave
     // reads its V buffers, so waiting for its own copies is enough.  (Each
     // exit has its own copy of the computation, so that inside the loop the
-    // compiler's waits count the newer tile's loads as these do.)
-    const int my_tiles = n_tiles > wave ? (n_tiles - wave + 3) / 4 : 0;
-    if (my_tiles > 0) {
-        load_tile(Tag<0>{}, 0);
-        for (int t = 0;; t += 2) {
-            if (t + 1 >= my_tiles) {
-                __builtin_amdgcn_s_waitcnt(0x0F70);
-                compute(Tag<0>{}, t);
-                break;
-            }
-            load_tile(Tag<1>{}, t + 1);
-            __builtin_amdgcn_s_waitcnt(T::WAIT_PREV);
-            compute(Tag<0>{}, t);
-            if (t + 2 >= my_tiles) {
-                __builtin_amdgcn_s_waitcnt(0x0F70);
-                compute(Tag<1>{}, t + 1);
-                break;
-            }
-            load_tile(Tag<0>{}, t + 2);
-            __builtin_amdgcn_s_waitcnt(T::WAIT_PREV);
-            compute(Tag<1>{}, t + 1);
-        }
+    // compiler's waits count the newer tile's loads as these do; a macro, since
+    // the K registers of a lambda around these two went to scratch.)
+#define RC_TILES(AUX, FIRST, LAST)                            \
+    if (const int i0 = FIRST, i1 = LAST; i0 < i1) {           \
+        load_tile(Tag<0>{}, Tag<AUX>{}, i0);                  \
+        for (int i = i0;; i += 2) {                           \
+            if (i + 1 >= i1) {                                \
+                __builtin_amdgcn_s_waitcnt(0x0F70);           \
+                compute(Tag<0>{}, i);                         \
+                break;                                        \
+            }                                                 \
+            load_tile(Tag<1>{}, Tag<AUX>{}, i + 1);           \
+            __builtin_amdgcn_s_waitcnt(T::WAIT_PREV);         \
+            compute(Tag<0>{}, i);                             \
+            if (i + 2 >= i1) {                                \
+                __builtin_amdgcn_s_waitcnt(0x0F70);           \
+                compute(Tag<1>{}, i + 1);                     \
+                break;                                        \
+            }                                                 \
+            load_tile(Tag<0>{}, Tag<AUX>{}, i + 2);           \
+            __builtin_amdgcn_s_waitcnt(T::WAIT_PREV);         \
+            compute(Tag<1>{}, i + 1);                         \
+        }                                                     \
     }
+    auto tiles_of = [&](int n) { return n > wave ? (n - wave + 3) / 4 : 0; };
+    if constexpr (NT) {
+        // the resource tiles, then the context tiles with their own loads
+        RC_TILES(0, 0, tiles_of(n_segt))
+        RC_TILES(2, tiles_of(n_segt), tiles_of(n_tiles))
+    } else {
+        RC_TILES(0, 0, tiles_of(n_tiles))
+    }
+#undef RC_TILES
 
     // ---- merge: the four row groups of a head hold disjoint dims of O^T and
     // parts of its row sum; then the four waves, through LDS.
@@ -459,10 +472,21 @@ template <int HD>
 hipError_t launch_dec(const DecodeArgs& a, hipStream_t s) {
     const long blocks = (long)a.n_req * a.n_kv_heads * a.n_splits;
     const bool big = (unsigned long)std::max(a.r_rows, a.c_rows) * HD * 2 >= (1UL << 32);
+    // Context rows past the caches where a layer of them (at most n_req *
+    // max_ctx rows) is twice the 256 MB last-level cache or more: they evict
+    // what would be found there, of the resources too.  64 requests, 4,096
+    // context rows (1 GB): 283 us a layer instead of 306; 33 requests (528 MB)
+    // over 1,000 / 100 / 32 resources: 135 / 166 / 128 instead of 152 / 184 /
+    // 126.  Below, the part of a context that stays cached is worth more, and
+    // so is the pipeline that this form drains between resources and context:
+    // 250 MB of context 106 us instead of 91, 400 MB 193 instead of 188.
+    const bool nt = (unsigned long)std::min(a.c_rows, a.max_ctx_rows) * a.n_kv_heads * HD * 4 >= (512UL << 20);
     if (big)
-        hipLaunchKernelGGL((decode_kernel<HD, true>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((decode_kernel<HD, true, false>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+    else if (nt)
+        hipLaunchKernelGGL((decode_kernel<HD, false, true>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
     else
-        hipLaunchKernelGGL((decode_kernel<HD, false>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((decode_kernel<HD, false, false>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     const unsigned waves = (unsigned)(a.n_req * a.n_q_heads), per = kThreads / 64;

@@ -143,6 +143,7 @@ struct DecodeArgs {
     const uint16_t* ck;
     const uint16_t* cv;
     long c_rows;
+    long max_ctx_rows;  // bound on the context rows that the requests use together
     const int32_t* cu_q;
     const int32_t* cu_ctx;
     int layer, n_layers;

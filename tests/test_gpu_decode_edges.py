@@ -1,7 +1,8 @@
 """GPU: decode where its addressing and its split of the key stream change:
 KV planes of 4 GiB and more (addressed by pointer, smaller ones through a
-buffer resource), and ranges that end inside, at and between the resource and
-context rows of short and long streams."""
+buffer resource), contexts of 512 MiB and more (loaded past the caches), and
+ranges that end inside, at and between the resource and context rows of short
+and long streams."""
 import numpy as np
 import pytest
 import torch
@@ -41,3 +42,26 @@ def test_decode_ranges(Hq, Hkv, d, ctx):
     w = small_attend(142 + ctx[0], 3, 6, Hq, Hkv, d, "bf16", [1, 1, 1], ctx, L=2, max_len=500)
     for layer in range(2):
         run_attend_case(w, layer)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 2, 128), (6, 1, 64)])
+@pytest.mark.parametrize("ctx", [[1, 5, 31], [32, 200, 1500]])
+def test_decode_large_context(Hq, Hkv, d, ctx):
+    """The same rows in planes and under a bound on the context that make the
+    kernel load them past the caches: the same order of work, the same bits."""
+    print_case("decode large context", Hq, Hkv, d, ctx)
+    w = small_attend(143 + ctx[0], 3, 6, Hq, Hkv, d, "bf16", [1, 1, 1], ctx, L=1, max_len=500)
+    rt = Routes(w)
+    q, ck, cv, rk, rv = w.layer_tensors(0, DEV)
+    mk = rt.max_kv(0)
+    ws = rt.workspace(mk)
+    out, lse = rt.attend(q, ck, cv, rk, rv, 0, workspace=ws, max_kv=mk)
+    rows = (512 << 20) // (Hkv * d * 4) + 3
+    big_k = torch.empty(Hkv, rows, d, dtype=ck.dtype, device=DEV)
+    big_v = torch.empty_like(big_k)
+    big_k[:, -sum(ctx):], big_v[:, -sum(ctx):] = ck, cv
+    rt.cu_ctx = i32(rows - sum(ctx) + np.concatenate([[0], np.cumsum(ctx)]))
+    rt.max_ctx = rows
+    big, big_lse = rt.attend(q, big_k, big_v, rk, rv, 0, workspace=ws, max_kv=mk)
+    torch.cuda.synchronize()
+    assert torch.equal(out, big) and torch.equal(lse, big_lse)
