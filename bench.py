@@ -436,10 +436,10 @@ def prune_row(dev, reps):
 USE_PLAN = True
 
 PROFILES = os.path.join(ROOT, "profiles")
-ENCODE_TRAFFIC = ("attn_mfma_encode_config2_traffic.md", ("attn_mfma.hip", "common.hpp", "kernels.hpp"))
+ENCODE_TRAFFIC = ("attn_mfma_encode_config2_traffic.md", ("attn_mfma.hip", "attn_tile.hpp", "common.hpp", "kernels.hpp"))
 PREFILL_TRAFFIC = {
-    3: ("attn_mfma_prefill_config3_traffic.md", ("attn_mfma.hip", "common.hpp", "kernels.hpp")),
-    4: ("attn_mfma_prefill_config4_traffic.md", ("attn_mfma.hip", "common.hpp", "kernels.hpp")),
+    3: ("attn_mfma_prefill_config3_traffic.md", ("attn_mfma.hip", "attn_tile.hpp", "common.hpp", "kernels.hpp")),
+    4: ("attn_mfma_prefill_config4_traffic.md", ("attn_mfma.hip", "attn_tile.hpp", "common.hpp", "kernels.hpp")),
 }
 DECODE_TRAFFIC = ("decode_config5_traffic.md", ("decode.hip", "common.hpp", "kernels.hpp"))
 

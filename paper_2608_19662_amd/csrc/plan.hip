@@ -12,9 +12,10 @@
 // in alternating direction, evens both out.
 //
 // One block per layer: the work of every pair (in key tiles, by the cost
-// model of the attention kernels), the (work, pair) keys ranked by counting
-// or, beyond 1024 pairs, in a bitonic sort in LDS, then the dealt order.  Keys are unique (ties fall to the lower pair
-// index), so the order is deterministic.
+// model of the attention kernels), the (work, pair) keys ranked or, beyond
+// 1024 pairs, put through a bitonic sort in LDS, then the dealt order.  Keys
+// are unique (ties fall to the lower pair index), so the order is
+// deterministic.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -23,7 +24,7 @@ namespace rc {
 namespace {
 
 constexpr int kPlanThreads = 1024;
-constexpr int kRankPairs = 1024;  // up to this many pairs are ranked by counting
+constexpr int kRankPairs = 1024;  // up to this many pairs are ranked, more are sorted
 
 __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArgs a) {
     __shared__ uint64_t key[kMaxPlanPairs];
