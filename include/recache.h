@@ -245,11 +245,14 @@ int recache_store_routes(int dtype, int layer, int n_layers, int n_res, const in
  * passage of the paper: decode (Fig. 2's final mask with one query per
  * request) splits each (request, group) key stream into chunks whose partial
  * outputs and log-sum-exps are merged afterwards; the workspace holds those
- * partials, fp32, n_req * n_q_heads * splits * (head_dim + 2) values (and is
- * enough for any smaller n_req at the same max_kv).
+ * partials, fp32, n_req * n_q_heads * splits * (head_dim + 2) values.  The
+ * size returned is the largest over this n_req and every smaller one (fewer
+ * requests can have more splits each), so that a program that sizes its
+ * workspace for its largest batch can keep it as requests leave.
  * max_kv is an upper bound on the keys a (request, group) can see in one layer
  * (route tokens + context), used only to choose the split count (and by
- * prefill the form of its blocks); 0 means "use max_ctx" (prefill: unknown).  Returns 0 for invalid sizes.  Pure host arithmetic.
+ * prefill the form of its blocks); 0 means "use max_ctx" (prefill: unknown).
+ * Returns 0 for invalid sizes.  Pure host arithmetic.
  */
 size_t recache_attend_workspace_bytes(int n_req, int max_q, int max_ctx, int max_kv,
                                       int n_q_heads, int n_kv_heads, int head_dim);
@@ -351,11 +354,11 @@ int recache_attend_plan(int n_layers, int n_req, int n_q_heads, int n_kv_heads,
  * Every call on one GPU shares that GPU's array and it keeps the last call's
  * contents, so calls that overlap on one GPU (several streams, several host
  * threads) race: serialise them.
- * Errors: those of recache_attend_cached, and RECACHE_EWORKSPACE when
- * recache_attend_workspace_bytes(...) for these sizes exceeds
- * RECACHE_NOALLOC_SCRATCH_BYTES (decode with n_req * n_q_heads * splits *
- * (head_dim + 2) fp32 partials; about 65K partial slots at head_dim 128),
- * checked before any HIP call; RECACHE_EHIP if the address lookup fails.
+ * Errors: those of recache_attend_cached, and RECACHE_EWORKSPACE when this
+ * batch's partials (decode: n_req * n_q_heads * splits * (head_dim + 2) fp32
+ * values) exceed RECACHE_NOALLOC_SCRATCH_BYTES (about 65K partial slots at
+ * head_dim 128), checked before any HIP call; RECACHE_EHIP if the address
+ * lookup fails.
  */
 #define RECACHE_NOALLOC_SCRATCH_BYTES (32 * 1024 * 1024)
 int recache_attend_cached_noalloc(int dtype, int layer, int n_layers, int n_req,

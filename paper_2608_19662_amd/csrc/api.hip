@@ -380,11 +380,8 @@ int recache_store_routes(int dtype, int layer, int n_layers, int n_res, const in
 size_t recache_attend_workspace_bytes(int n_req, int max_q, int max_ctx, int max_kv,
                                       int n_q_heads, int n_kv_heads, int head_dim) {
     if (n_req <= 0 || max_q != 1 || n_q_heads <= 0 || n_kv_heads <= 0 || head_dim <= 0) return 0;
-    const int kv = max_kv > 0 ? max_kv : max_ctx;
-    if (n_q_heads < n_kv_heads)
-        return decode_workspace_bytes(n_req, n_q_heads, head_dim, decode_splits(n_req, n_kv_heads, kv));
-    return std::max(decode_workspace_bytes(n_req, n_q_heads, head_dim, decode_splits(n_req, n_kv_heads, kv)),
-                    decode_workspace_bytes(1, (int)decode_slots(n_req, n_q_heads, n_kv_heads, kv), head_dim, 1));
+    return decode_workspace_bytes(decode_max_parts(n_req, n_kv_heads, max_kv > 0 ? max_kv : max_ctx), n_q_heads,
+                                  head_dim);
 }
 
 }  // extern "C"
@@ -481,9 +478,8 @@ int recache_attend_cached(int dtype, int layer, int n_layers, int n_req, const i
         return hip_status(launch_attn_f32(a, false, s), "attend (fp32) launch");
     }
     if (max_q == 1) {
-        const int kv = max_kv > 0 ? max_kv : max_ctx;
-        const int n_splits = decode_splits(n_req, n_kv_heads, kv);
-        const size_t need = decode_workspace_bytes(n_req, n_q_heads, head_dim, n_splits);
+        const int n_splits = decode_splits(n_req, n_kv_heads, max_kv > 0 ? max_kv : max_ctx);
+        const size_t need = decode_workspace_bytes((long)n_req * n_splits, n_q_heads, head_dim);
         REQUIRE(workspace && workspace_bytes >= need, RECACHE_EWORKSPACE,
                 "decode needs a %zu-byte workspace, got %zu", need, workspace ? workspace_bytes : 0);
         DecodeArgs a{};
@@ -640,11 +636,13 @@ int recache_attend_cached_noalloc(int dtype, int layer, int n_layers, int n_req,
                            ctx_v, ctx_rows, res_k, res_v, res_rows, cu_kept, res_off, route_off,
                            route_res, route_tokens, out);
     if (rc_) return rc_;
-    // the same workspace rule as recache_attend_cached: only bf16 decode uses one
-    const size_t need = dtype == RECACHE_BF16
-                            ? recache_attend_workspace_bytes(n_req, max_q, max_ctx, max_kv,
-                                                             n_q_heads, n_kv_heads, head_dim)
-                            : 0;
+    // the same workspace rule as recache_attend_cached: only bf16 decode uses
+    // one, of this batch's own partials
+    const size_t need =
+        dtype == RECACHE_BF16 && max_q == 1
+            ? decode_workspace_bytes((long)n_req * decode_splits(n_req, n_kv_heads, max_kv > 0 ? max_kv : max_ctx),
+                                     n_q_heads, head_dim)
+            : 0;
     REQUIRE(need <= (size_t)RECACHE_NOALLOC_SCRATCH_BYTES, RECACHE_EWORKSPACE,
             "decode needs %zu bytes of split partials, more than the %zu-byte static scratch of "
             "the allocation-free entry point (use recache_attend_cached with a workspace)",

@@ -498,9 +498,10 @@ hipError_t launch_dec(const DecodeArgs& a, hipStream_t s) {
 
 namespace {
 
-// Blocks that a grid is filled to where streams are short of kKeysPerBlock
-// each: two per CU, at 128 keys (one tile per wave) or more.
-constexpr long kFewBlocks = 512;
+// Blocks that a grid is filled to at 512 keys or more each, and where that
+// leaves CUs idle at 128 keys (one tile per wave) or more: three rounds of two
+// blocks per CU, and one.
+constexpr long kManyBlocks = 1536, kFewBlocks = 512;
 
 long split_limit(long units, int max_kv, long blocks, int keys) {
     return std::min({(blocks + units - 1) / units, ((long)max_kv + keys - 1) / keys, 64L});
@@ -514,20 +515,28 @@ long split_limit(long units, int max_kv, long blocks, int keys) {
 // kernel 7.2 us instead of 10.5, the merge of the splits 4.7 and 3.9).
 int decode_splits(int n_req, int n_kv_heads, int max_kv) {
     const long units = (long)n_req * n_kv_heads;
-    const long s = split_limit(units, max_kv, 1536, 512);
+    const long s = split_limit(units, max_kv, kManyBlocks, 512);
     const long few = std::min(kFewBlocks / units, split_limit(units, max_kv, kFewBlocks, 128));
     return (int)std::max({s, few, 1L});
 }
 
-long decode_slots(int n_req, int n_q_heads, int n_kv_heads, int max_kv) {
-    const long units = (long)n_req * n_kv_heads, r = n_q_heads / n_kv_heads;
-    const long few = std::min(kFewBlocks, units * (((long)max_kv + 127) / 128));
-    return std::max(units * decode_splits(n_req, n_kv_heads, max_kv), few) * r;
+// Splits fall as requests are added, so requests times splits is largest at
+// the last request count of some split count: the walk goes from n_req to
+// smaller batches, to the largest one that can have another split each time.
+long decode_max_parts(int n_req, int n_kv_heads, int max_kv) {
+    const long g = n_kv_heads, by512 = ((long)max_kv + 511) / 512, by128 = ((long)max_kv + 127) / 128;
+    const int top = decode_splits(1, n_kv_heads, max_kv);
+    long n = n_req, most = 0;
+    for (;;) {
+        const long c = decode_splits((int)n, n_kv_heads, max_kv);
+        most = std::max(most, n * c);
+        if (c >= top) return most;
+        n = std::min(n - 1, std::max(c < by512 ? (kManyBlocks - 1) / c : 0, c < by128 ? kFewBlocks / (c + 1) : 0) / g);
+    }
 }
 
-size_t decode_workspace_bytes(int n_req, int n_q_heads, int head_dim, int n_splits) {
-    const size_t slots = (size_t)n_req * n_q_heads * n_splits;
-    return slots * head_dim * sizeof(float) + slots * 2 * sizeof(float);
+size_t decode_workspace_bytes(long parts, int n_q_heads, int head_dim) {
+    return (size_t)parts * n_q_heads * (head_dim + 2) * sizeof(float);
 }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s) {

@@ -156,11 +156,12 @@ struct DecodeArgs {
     const int32_t* plan;  // work order of the (request, group) pairs, or NULL
 };
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
-size_t decode_workspace_bytes(int n_req, int n_q_heads, int head_dim, int n_splits);
 int decode_splits(int n_req, int n_kv_heads, int max_kv);
-// Partial slots for a batch of n_req requests or any smaller one (a program
-// that sizes its workspace for its largest batch keeps it for the others).
-long decode_slots(int n_req, int n_q_heads, int n_kv_heads, int max_kv);
+// The most partials per query head, requests times splits, that a batch of
+// n_req requests or any smaller one makes (a program that sizes its workspace
+// for its largest batch keeps it for the others).
+long decode_max_parts(int n_req, int n_kv_heads, int max_kv);
+size_t decode_workspace_bytes(long parts, int n_q_heads, int head_dim);
 
 // Work order of the attend kernels (plan.hip): per layer, the pairs
 // b * n_kv_heads + g sorted by their work, longest first, dealt in snake order

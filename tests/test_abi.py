@@ -125,6 +125,19 @@ def test_workspace_sizes():
     assert rc.attend_workspace_bytes(8, 2048, 2048, 0, 32, 8, 128) == 0
 
 
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (8, 8, 64), (28, 4, 128), (8, 1, 128), (6, 2, 64)])
+def test_workspace_covers_every_smaller_batch(Hq, Hkv, d):
+    """A workspace sized for n requests is enough for any m <= n at the same
+    max_kv, and no larger than the largest of them needs (a call without a
+    workspace states its own need and launches nothing)."""
+    for max_kv in (1, 100, 129, 513, 1000, 8000, 40000):
+        most = 0
+        for m in range(1, 320):
+            assert att(n_req=m, total_q=m, max_ctx=16, max_kv=max_kv, Hq=Hq, Hkv=Hkv, d=d) == rc.EWORKSPACE
+            most = max(most, int(re.search(r"needs a (\d+)-byte", rc.last_error()).group(1)))
+            assert rc.attend_workspace_bytes(m, 1, 16, max_kv, Hq, Hkv, d) == most, (max_kv, m)
+
+
 def test_prune_and_routes_reject():
     L = rc.lib()
     assert L.recache_prune_gather(1, 2, FAKE, FAKE, FAKE, 10, 11, 8, 128, FAKE, FAKE, FAKE, FAKE,
