@@ -340,16 +340,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args
         float den = 0.f;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            // a wave that saw no visible key carries no weight (its NaN sum,
-            // from a NaN logit, does)
+            // A wave that saw no visible key carries no weight (its O and sum
+            // are 0; its NaN sum, from a NaN logit, counts).  One whose weight
+            // underflows still passes on an infinity or NaN.
             const float mw = sm.ml[w][col][0], lw = sm.ml[w][col][1];
             const float f = mw == -INFINITY ? (lw == 0.f ? 0.f : lw) : exp2f(mw - mx);
             const f32x4 o = *reinterpret_cast<const f32x4*>(&sm.v[w][col * HD + ((c ^ (col % LPR)) << 2)]);
-            if (f != 0.f) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) num[e] += f * o[e];
-                den += f * lw;
-            }
+            for (int e = 0; e < 4; ++e) num[e] += f * o[e];
+            den += f * lw;
         }
         const float inv = 1.0f / den;
 #pragma unroll

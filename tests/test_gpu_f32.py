@@ -79,3 +79,26 @@ def test_f32_unseen_values_do_not_matter(bad):
     assert not torch.isfinite(b[23:, :, 5]).any()
     other = [i for i in range(128) if i != 5]
     assert torch.equal(a[23:, :, other], b[23:, :, other])
+
+
+@pytest.mark.parametrize("key", [5, 40, 90, 127])
+def test_f32_unlikely_values_still_count(key):
+    """A visible key whose weight underflows beside the others' keeps its say
+    where its value row or its logit is not finite, whichever wave holds it:
+    0 times infinity is no zero, and a NaN logit makes the row NaN."""
+    print_case("f32 unlikely values", key)
+    w = small_attend(115, 1, 2, 8, 2, 128, "f32", [3], [130], L=1, mask_p=0.0)
+    rt = Routes(w)
+    q, ck, cv, rk, rv = w.layer_tensors(0, DEV)
+    q[:] = 1.0
+    tile = key // 32 * 32
+    ck[:, tile:tile + 32] -= 30.0  # logits of this tile about 340 below the rest
+    cv[:, key, 5] = float("inf")
+    a, _ = rt.attend(q, ck, cv, rk, rv, 0)
+    ck[:, key, 0] = float("nan")
+    b, bl = rt.attend(q, ck, cv, rk, rv, 0)
+    torch.cuda.synchronize()
+    # (query 0 does not see the last two of the 130 context rows)
+    assert not torch.isfinite(a[:, :, 5]).any()
+    assert torch.isfinite(a[:, :, [i for i in range(128) if i != 5]]).all()
+    assert torch.isnan(b).all() and torch.isnan(bl).all()
