@@ -39,6 +39,10 @@ EDGES = [1, 2, 7, 8, 9, 31, 32, 33, 65]
     ("split 8", 9, 6, 2, 64, EDGES, 500),
     ("split 4", 40, 32, 8, 128, EDGES, 500),              # 320 blocks
     ("split 4", 36, 24, 8, 64, EDGES, 500),
+    ("split 8, blocks numbered over the columns", 41, 8, 1, 128, [1] * 20 + [128] + [1, 3, 9, 1] * 5, 500),
+    ("split 8, blocks numbered over the columns", 9, 28, 4, 64, [100, 1, 1, 37, 1, 1, 1, 1, 5], 500),
+    ("split 4, blocks numbered over the columns", 300, 8, 1, 128, [1] * 270 + [65] + [2] * 29, 500),
+    ("split 4, blocks numbered over the columns", 256, 8, 2, 64, [33] + [1] * 255, 500),
     ("split 4, one block per request", 70, 32, 8, 128, [1, 2, 7, 8], 500),
     ("split 4, one block per request", 70, 56, 8, 64, [1, 4], 500),
     ("blocks of 4", 66, 24, 8, 128, EDGES, 500),          # groups of 3: pairs cross row blocks
