@@ -328,7 +328,7 @@ int recache_build_routes(int n_req, const int32_t* req_res_off, const int32_t* r
     REQUIRE(req_res_off && req_res && route_mask && cu_kept && route_off && route_res && route_tokens,
             RECACHE_EINVAL, "null pointer argument");
     (void)hipGetLastError();
-    return hip_status(launch_build_routes(n_req, req_res_off, req_res, n_res, n_layers, n_kv_heads,
+    return hip_status(launch_build_routes(n_req, req_res_off, req_res, total_req_res, n_res, n_layers, n_kv_heads,
                                           route_mask, cu_kept, route_off, route_res, route_tokens,
                                           as_stream(stream)),
                       "recache_build_routes launch");

@@ -78,10 +78,19 @@ __device__ __forceinline__ int2 stage_resource(int j, int j1, int n_res, const i
     return make_int2(r, cu_kept[r + 1] - cu_kept[r]);
 }
 
-// Index in route_off of the last entry of slice sl (64 entries of a request,
-// fewer in its last slice).
-__device__ __forceinline__ size_t slice_last(long sl, int n_slices, int LG) {
-    return (size_t)(sl / n_slices) * LG + min((int)(sl % n_slices) * 64 + 64, LG);
+// Slices of the entries, one per wave: 64 entries of a request, fewer in its
+// last slice, or with FLAT any 64 consecutive entries.  Index in route_off of
+// the last entry of slice sl.
+struct Slices {
+    int n;        // slices in all
+    int per_req;  // of each request
+    int LG, E;    // entries of a request, and in all
+};
+
+template <bool FLAT>
+__device__ __forceinline__ size_t slice_last(const Slices& z, uint32_t sl) {
+    if (FLAT) return min((long)sl * 64 + 64, (long)z.E);
+    return (size_t)(sl / (uint32_t)z.per_req) * z.LG + min((int)(sl % (uint32_t)z.per_req) * 64 + 64, z.LG);
 }
 
 // Entry e = (b * L + l) * G + g, one wave per slice of 64 entries of a request.
@@ -91,27 +100,54 @@ __device__ __forceinline__ size_t slice_last(long sl, int n_slices, int LG) {
 // the last one of the slice before, and the resource ids in request order.
 // Bound by latency: 18,432 entries of 32 resources each in 4.8 and 4.9 us (a
 // thread per entry that walked the list itself, on 72 CUs: 13.7 and 11.5).
-template <bool FILL>
+// FLAT: lanes of several requests, each of which walks its own list.
+template <bool FILL, bool FLAT>
 __global__ __launch_bounds__(64) void route_walk_kernel(
-    int n_slices, int LG, int n_res, const int32_t* __restrict__ req_res_off,
+    const Slices z, int n_res, const int32_t* __restrict__ req_res_off,
     const int32_t* __restrict__ req_res, const uint8_t* __restrict__ mask,
     const int32_t* __restrict__ cu_kept, int32_t* __restrict__ route_off,
     int32_t* __restrict__ route_tokens, int32_t* __restrict__ route_res) {
-    const int b = blockIdx.x / n_slices, lane = threadIdx.x;
-    const int lg = (blockIdx.x % n_slices) * 64 + lane;  // (layer, group) of this lane
-    const bool in = lg < LG;
+    const int LG = z.LG, lane = threadIdx.x;
+    const uint32_t sl = blockIdx.x;
+    int b, lg;  // request and (layer, group) of this lane
+    bool in, last;  // whether its entry exists, and ends its slice
+    if constexpr (FLAT) {
+        const uint32_t e = sl * 64 + lane;
+        b = (int)(min(e, (uint32_t)z.E - 1) / (uint32_t)LG);
+        lg = (int)(e - (uint32_t)b * LG);
+        in = e < (uint32_t)z.E;
+        last = lane == 63 || e == (uint32_t)z.E - 1;
+    } else {
+        b = (int)(sl / (uint32_t)z.per_req);
+        lg = (int)(sl % (uint32_t)z.per_req) * 64 + lane;
+        in = lg < LG;
+        last = lane == 63 || lg == LG - 1;
+    }
     const uint8_t* m = mask + (in ? lg : 0);
     const int j0 = req_res_off[b], j1 = req_res_off[b + 1];
     const size_t e = (size_t)b * LG + lg;
     int cnt = 0, tok = 0, w = 0, incl = 0;
     if constexpr (FILL) {
-        const int base = blockIdx.x > 0 ? route_off[slice_last(blockIdx.x - 1L, n_slices, LG)] : 0;
-        const bool last = lane == 63 || lg == LG - 1;  // holds its final value already
+        const int base = sl > 0 ? route_off[slice_last<FLAT>(z, sl - 1)] : 0;
+        // (a slice's last entry holds its final value already)
         incl = in ? (last ? route_off[e + 1] : base + route_off[e + 1]) : 0;
         const int before = __shfl_up(incl, 1);
         w = lane == 0 ? base : before;
     }
-    for (int js = j0; js < j1; js += kRouteStage) {
+    if constexpr (FLAT) {
+#pragma unroll 4
+        for (int j = j0; j < (in ? j1 : j0); ++j) {
+            const int r = req_res[j];
+            if (r < 0 || r >= n_res || !m[(size_t)r * LG]) continue;
+            if constexpr (FILL) {
+                route_res[w++] = r;
+            } else {
+                ++cnt;
+                tok += cu_kept[r + 1] - cu_kept[r];
+            }
+        }
+    }
+    for (int js = j0; !FLAT && js < j1; js += kRouteStage) {
         const int2 mine = stage_resource(js + lane, j1, n_res, req_res, cu_kept);
         const int n = min(kRouteStage, j1 - js);
         constexpr int U = 16;
@@ -138,8 +174,8 @@ __global__ __launch_bounds__(64) void route_walk_kernel(
         }
     }
     if constexpr (FILL) {
-        if (in && !(lane == 63 || lg == LG - 1)) route_off[e + 1] = incl;
-        if (blockIdx.x == 0 && lane == 0) route_off[0] = 0;
+        if (in && !last) route_off[e + 1] = incl;
+        if (sl == 0 && lane == 0) route_off[0] = 0;
     } else {
         int s = cnt;
         for (int o = 1; o < 64; o <<= 1) {
@@ -156,17 +192,17 @@ __global__ __launch_bounds__(64) void route_walk_kernel(
 // The slices' totals (their last entries of route_off) become the entries'
 // final values: an inclusive scan over the slices by one block.  (Over all
 // entries, 18,432 of them: 11.3 us; over their 320 slices 4.6.)
-__global__ __launch_bounds__(1024) void route_scan_kernel(long n, int n_slices, int LG,
-                                                          int32_t* __restrict__ route_off) {
+template <bool FLAT>
+__global__ __launch_bounds__(1024) void route_scan_kernel(const Slices z, int32_t* __restrict__ route_off) {
     __shared__ int wave_tot[2][16];  // alternate buffers: one barrier per chunk suffices
     int carry = 0, k = 0;
-    for (long base = 0; base < n; base += 1024, k ^= 1) {
+    for (long base = 0; base < z.n; base += 1024, k ^= 1) {
         const long sl = base + threadIdx.x;
-        const size_t at = slice_last(min(sl, n - 1), n_slices, LG);
-        const int v = sl < n ? route_off[at] : 0;
+        const size_t at = slice_last<FLAT>(z, (uint32_t)min(sl, z.n - 1L));
+        const int v = sl < z.n ? route_off[at] : 0;
         int total;
         const int before = carry + block_exclusive_scan<16>(v, wave_tot[k], &total);
-        if (sl < n) route_off[at] = before + v;
+        if (sl < z.n) route_off[at] = before + v;
         carry += total;
     }
 }
@@ -383,22 +419,35 @@ hipError_t launch_prune_gather(int elem_bytes, int n_res, const int32_t* cu_len,
 }
 
 hipError_t launch_build_routes(int n_req, const int32_t* req_res_off, const int32_t* req_res,
-                               int n_res, int n_layers, int n_kv_heads, const uint8_t* mask,
+                               int total_req_res, int n_res, int n_layers, int n_kv_heads, const uint8_t* mask,
                                const int32_t* cu_kept, int32_t* route_off, int32_t* route_res,
                                int32_t* route_tokens, hipStream_t s) {
-    const int LG = n_layers * n_kv_heads, slices = (LG + 63) / 64;
-    const long blocks = (long)n_req * slices;
-    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((route_walk_kernel<false>), dim3((unsigned)blocks), dim3(64), 0, s, slices, LG, n_res,
-                       req_res_off, req_res, mask, cu_kept, route_off, route_tokens, route_res);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(1024), 0, s, blocks, slices, LG, route_off);
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((route_walk_kernel<true>), dim3((unsigned)blocks), dim3(64), 0, s, slices, LG, n_res,
-                       req_res_off, req_res, mask, cu_kept, route_off, route_tokens, route_res);
-    return hipGetLastError();
+    Slices z{};
+    z.LG = n_layers * n_kv_heads;
+    z.E = n_req * z.LG;
+    z.per_req = (z.LG + 63) / 64;
+    const long n = (long)n_req * z.per_req;
+    // A wave for each request costs 1.7 us per thousand of them where its lanes
+    // are mostly idle (few entries per request) and there are more waves than
+    // the CUs hold; lanes that walk lists themselves, 0.4 us per resource.  One
+    // entry each, 20,000 requests: lists of 2 in 12.6 us instead of 44, of 30 in
+    // 22 instead of 56; 4,097 requests of 64 resources: 39 instead of 26.
+    const bool flat = z.LG <= 16 && n > 4096 && (long)total_req_res * 256 <= n * n_req;
+    z.n = flat ? (z.E + 63L) / 64 : n;
+    auto go = [&](auto count, auto scan, auto fill) {
+        hipLaunchKernelGGL(count, dim3((unsigned)z.n), dim3(64), 0, s, z, n_res, req_res_off, req_res, mask, cu_kept,
+                           route_off, route_tokens, route_res);
+        hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL(scan, dim3(1), dim3(1024), 0, s, z, route_off);
+        err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL(fill, dim3((unsigned)z.n), dim3(64), 0, s, z, n_res, req_res_off, req_res, mask, cu_kept,
+                           route_off, route_tokens, route_res);
+        return hipGetLastError();
+    };
+    return flat ? go(route_walk_kernel<false, true>, route_scan_kernel<true>, route_walk_kernel<true, true>)
+                : go(route_walk_kernel<false, false>, route_scan_kernel<false>, route_walk_kernel<true, false>);
 }
 
 }  // namespace rc

@@ -124,7 +124,7 @@ hipError_t launch_store_routes(int elem_bytes, int layer, int n_res, const int32
 
 // Route CSR build.
 hipError_t launch_build_routes(int n_req, const int32_t* req_res_off, const int32_t* req_res,
-                               int n_res, int n_layers, int n_kv_heads, const uint8_t* mask,
+                               int total_req_res, int n_res, int n_layers, int n_kv_heads, const uint8_t* mask,
                                const int32_t* cu_kept, int32_t* route_off, int32_t* route_res,
                                int32_t* route_tokens, hipStream_t s);
 

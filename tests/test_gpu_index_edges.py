@@ -18,6 +18,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n_req,pool,L,G,per", [
     (1, 1, 1, 1, (1, 2)), (3, 70, 8, 8, (0, 70)), (2, 130, 13, 5, (63, 66)), (5, 200, 36, 8, (0, 180)),
     (1030, 9, 1, 3, (0, 4)),
+    # many requests of few entries: lanes of several requests in a wave
+    (4097, 30, 1, 1, (0, 12)), (5001, 40, 5, 3, (0, 18)), (8200, 6, 2, 8, (0, 6)), (20001, 9, 1, 3, (0, 3)),
+    # and where a wave takes one of them: long lists, as many waves as fit
+    (4097, 70, 1, 2, (30, 70)), (4096, 9, 2, 2, (0, 4)),
 ])
 def test_routes_edges(n_req, pool, L, G, per):
     print("case: route edges", n_req, pool, L, G, per, flush=True)
