@@ -49,6 +49,8 @@
  * - Element types: RECACHE_F32 (float) or RECACHE_BF16 (bfloat16); all
  *   floating tensors of one call share the dtype.  bf16 math accumulates in
  *   fp32; outputs are rounded to nearest even.  head_dim is 64 or 128.
+ * - Q, K, V, O and the caches and stores start on 16-byte boundaries; in fp32
+ *   attention any float will do (off those boundaries it is slower).
  * - The bf16 encode and prefill kernels address each KV plane (one KV head's
  *   rows of a cache or of the context, a layer's route-compacted store)
  *   through 32-bit byte offsets: a plane of 4 GiB or more (16.7M rows at

@@ -33,6 +33,7 @@
 // encode in 140 us (one wave per row and head, a shuffle reduction per key:
 // 965 us), two requests of 150 to 250 queries over them attend in 73 us (669).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -48,6 +49,7 @@ constexpr int kKeys = 32;     // keys per wave tile
 constexpr int kMaxSeg = 1024; // route segments per pass over the segment table
 
 typedef __attribute__((address_space(3))) void lds_void;
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int HD>
 struct F32Smem {
@@ -60,12 +62,16 @@ struct F32Smem {
     alignas(16) float v[kWaves][kKeys * HD];
 };
 
-template <int HD, bool ENCODE>
+// DWORD: a tensor that is not on 16 bytes (a view that starts at any float).
+// Its rows are read and written as four floats each way, and V copied into LDS
+// dword by dword.
+template <int HD, bool ENCODE, bool DWORD>
 __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args a) {
     constexpr int NJ = HD / 8;    // 8-dim steps of S^T (four MFMAs each)
     constexpr int NDB = HD / 32;  // 32-dim blocks of O^T
     constexpr int LPR = HD / 4;   // lanes per row of a V copy (16 bytes each)
     constexpr int NVC = kKeys * HD / 256;  // 1 KB copies per V tile
+    using vec = std::conditional_t<DWORD, f32x4_dword, f32x4>;  // four floats in memory
     __shared__ F32Smem<HD> sm;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -117,7 +123,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args
         const long row = max(0L, min((long)q_row0 + my_row, max_q));
         const float* qp = a.q + ((size_t)row * a.n_q_heads + g * R + my_head) * HD + half * 4;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) qf[j] = *reinterpret_cast<const f32x4*>(qp + j * 8);
+        for (int j = 0; j < NJ; ++j) qf[j] = *reinterpret_cast<const vec*>(qp + j * 8);
     }
     if constexpr (ENCODE) {
         // RoPE at the resource-local position: cos / sin of the block's rows
@@ -209,9 +215,18 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args
             code = row_code(t);
             const float* kp = (code < 0 ? ctx_k + (size_t)(~code) * HD : seg_k + (size_t)code * HD) + half * 4;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(kp + j * 8);
+            for (int j = 0; j < NJ; ++j) kf[j] = *reinterpret_cast<const vec*>(kp + j * 8);
         };
         auto copy_v = [&]() {  // of the tile whose row codes are in `code`
+            if constexpr (DWORD) {
+#pragma unroll 4
+                for (int c = 0; c < kKeys * HD / 64; ++c) {  // 64 floats of one row
+                    const int rc_ = __builtin_amdgcn_readlane(code, c * 64 / HD);
+                    const float* vp = rc_ < 0 ? ctx_v + (size_t)(~rc_) * HD : seg_v + (size_t)rc_ * HD;
+                    __builtin_amdgcn_global_load_lds(vp + c * 64 % HD + lane, (lds_void*)(vbuf + c * 64), 4, 0, 0);
+                }
+                return;
+            }
 #pragma unroll
             for (int c = 0; c < NVC; ++c) {
                 // lane k holds key k's code (the byte address folds into the instruction)
@@ -353,7 +368,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args
         const float inv = 1.0f / den;
 #pragma unroll
         for (int e = 0; e < 4; ++e) num[e] *= inv;
-        *reinterpret_cast<f32x4*>(a.out + ((size_t)row * a.n_q_heads + head) * HD + c * 4) = num;
+        *reinterpret_cast<vec*>(a.out + ((size_t)row * a.n_q_heads + head) * HD + c * 4) = num;
         if (a.lse && c == 0)
             a.lse[(size_t)head * a.lse_rows + row] = (mx + log2f(den)) * 0.69314718055994531f;
     }
@@ -368,19 +383,18 @@ hipError_t launch_attn_f32(const AttnF32Args& a, bool encode, hipStream_t stream
     const long blocks = (long)b.n_cb * a.n_units * a.n_kv_heads;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(kThreads);
+    const uintptr_t at = (uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.k | (uintptr_t)a.v | (uintptr_t)a.ck |
+                         (uintptr_t)a.cv;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, b);
+        return hipGetLastError();
+    };
     if (a.head_dim == 128) {
-        if (encode)
-            hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, block, 0, stream, b);
-        else
-            hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, block, 0, stream, b);
-    } else {
-        if (encode)
-            hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, block, 0, stream, b);
-        else
-            hipLaunchKernelGGL((attn_f32_kernel<64, false>), grid, block, 0, stream, b);
+        if (at & 15) return encode ? go(attn_f32_kernel<128, true, true>) : go(attn_f32_kernel<128, false, true>);
+        return encode ? go(attn_f32_kernel<128, true, false>) : go(attn_f32_kernel<128, false, false>);
     }
-    return hipGetLastError();
+    if (at & 15) return encode ? go(attn_f32_kernel<64, true, true>) : go(attn_f32_kernel<64, false, true>);
+    return encode ? go(attn_f32_kernel<64, true, false>) : go(attn_f32_kernel<64, false, false>);
 }
 
 }  // namespace rc

@@ -14,7 +14,8 @@ import pytest
 import torch
 
 import oracle
-from gpu_helpers import DEV, Routes, check
+from gpu_helpers import DEV, Routes, check, i32
+from paper_2608_19662_amd import recache as rc
 from paper_2608_19662_amd.workloads import EncodeWorkload
 
 from test_gpu_parity import gpu_encode, many_segments, print_case, run_attend_case, small_attend
@@ -102,3 +103,39 @@ def test_f32_unlikely_values_still_count(key):
     assert not torch.isfinite(a[:, :, 5]).any()
     assert torch.isfinite(a[:, :, [i for i in range(128) if i != 5]]).all()
     assert torch.isnan(b).all() and torch.isnan(bl).all()
+
+
+def at_float(t, n):
+    """A copy of t that starts n floats behind a 16-byte boundary."""
+    b = torch.empty(t.numel() + 4, dtype=t.dtype, device=DEV)
+    v = b[n:n + t.numel()].view(t.shape)
+    assert v.data_ptr() % 16 == 4 * n
+    return v.copy_(t)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+@pytest.mark.parametrize("Hq,Hkv,d", [(6, 2, 64), (20, 4, 128)])
+def test_f32_tensors_at_any_float(Hq, Hkv, d, n):
+    """Attention over tensors that start at any float: the bits of the same
+    call on 16-byte boundaries, with all of them shifted and with one."""
+    print_case("f32 alignment", Hq, Hkv, d, n)
+    w = small_attend(116, 3, 5, Hq, Hkv, d, "f32", [6, 1, 33], [39, 1, 140], L=1)
+    rt = Routes(w)
+    ts = w.layer_tensors(0, DEV)
+    assert all(t.data_ptr() % 16 == 0 for t in ts)
+    want, want_lse = rt.attend(*ts, 0)
+    for which in [range(5), *([i] for i in range(5))]:
+        got, lse = rt.attend(*[at_float(t, n) if i in which else t for i, t in enumerate(ts)], 0)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want) and torch.equal(lse, want_lse), which
+
+    e = EncodeWorkload(seed=117, lengths=np.array([1, 33, 129], np.int32), n_q_heads=Hq, n_kv_heads=Hkv,
+                       head_dim=d, dtype="f32", rope_base=1e4)
+    q, k, v = (t.to(DEV) for t in e.tensors("cpu"))
+    want, kc, vc, want_lse = gpu_encode(e, q, k, v)
+    for shift in (lambda t: at_float(t, n), lambda t: t):
+        got = at_float(torch.zeros_like(q), n)
+        lse = torch.empty_like(want_lse)
+        rc.encode_attention(shift(q), shift(kc), shift(vc), i32(e.cu_len), 129, e.rope_base, got, lse=lse)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want) and torch.equal(lse, want_lse)
