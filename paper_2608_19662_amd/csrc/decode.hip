@@ -214,14 +214,14 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
             row = min(c0 + p, c_last);
         }
         row = max(row, 0);
-        const int off = BIG ? row : row * T::ROWB;
+        const uint32_t off = BIG ? (uint32_t)row : (uint32_t)row * T::ROWB;  // (a plane may reach 4 GiB)
         const uint64_t kp = uniform64((uint64_t)((seg ? a.rk : a.ck) + (size_t)g * (seg ? a.r_gstride : a.c_rows) * HD));
         const uint64_t vp = uniform64((uint64_t)((seg ? a.rv : a.cv) + (size_t)g * (seg ? a.r_gstride : a.c_rows) * HD));
         char* dst = buf ? v_st1 : v_st0;
         if constexpr (BIG) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(l16 * 4 + kb * 64, off);
+                const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(l16 * 4 + kb * 64, (int)off);
                 const uint64_t src = kp + r * T::ROWB + grp * 16;
 #pragma unroll
                 for (int ks = 0; ks < T::NKS; ++ks) kreg[buf][kb][ks] = ((const global_u32x4*)src)[ks * 4];
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
 #pragma unroll
             for (int j = 0; j < T::NJ; ++j) {
                 const uint64_t r =
-                    (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(lane / T::CPR * 4 + j * T::RPI * 4, off);
+                    (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(lane / T::CPR * 4 + j * T::RPI * 4, (int)off);
                 const uint64_t src = vp + r * T::ROWB + v_lane[j & 1];
                 __builtin_amdgcn_global_load_lds((const uint16_t*)src, (lds_void*)(dst + j * 1024), 16, 0, 0);
             }
@@ -241,14 +241,15 @@ __global__ __launch_bounds__(kThreads, 2) void decode_kernel(const DecodeArgs a)
                 __builtin_amdgcn_make_buffer_rsrc((void*)vp, (short)0, bytes, kBufferFlags);
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const int o = __builtin_amdgcn_ds_bpermute(l16 * 4 + kb * 64, off) + grp * 16;
+                const uint32_t o = (uint32_t)__builtin_amdgcn_ds_bpermute(l16 * 4 + kb * 64, (int)off) + grp * 16;
 #pragma unroll
                 for (int ks = 0; ks < T::NKS; ++ks)
-                    kreg[buf][kb][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, o + ks * 64, 0, AUX);
+                    kreg[buf][kb][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, (int)(o + ks * 64), 0, AUX);
             }
 #pragma unroll
             for (int j = 0; j < T::NJ; ++j) {
-                const int o = __builtin_amdgcn_ds_bpermute(lane / T::CPR * 4 + j * T::RPI * 4, off) + (int)v_lane[j & 1];
+                const uint32_t o =
+                    (uint32_t)__builtin_amdgcn_ds_bpermute(lane / T::CPR * 4 + j * T::RPI * 4, (int)off) + v_lane[j & 1];
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void*)(dst + j * 1024), 16, (int)o, 0, 0, AUX);
             }
         }

@@ -1,6 +1,6 @@
 """GPU: decode where its addressing and its split of the key stream change:
 KV planes of 4 GiB and more (addressed by pointer, smaller ones through a
-buffer resource), contexts of 512 MiB and more (loaded past the caches), and
+buffer resource, whose offsets past 2 GiB have their top bit set), contexts of 512 MiB and more (loaded past the caches), and
 ranges that end inside, at and between the resource and context rows of short
 and long streams."""
 import numpy as np
@@ -31,6 +31,36 @@ def test_decode_plane_of_4_gib(d):
     big_k[:, -333:], big_v[:, -333:] = ck, cv
     rt.cu_ctx = i32([rows - 333, rows])
     big, big_lse = rt.attend(q, big_k, big_v, rk, rv, 0, workspace=ws, max_kv=mk)
+    torch.cuda.synchronize()
+    assert torch.equal(out, big) and torch.equal(lse, big_lse)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("end", [(1 << 31) + (1 << 14), (3 << 30) + (1 << 10), (1 << 32) - (1 << 9)])
+def test_decode_plane_past_2_gib(d, end):
+    """The same rows across 2 GiB, past it and at the end of the largest plane
+    that has 32-bit offsets, for the context and for the resources: the bits of
+    a small plane."""
+    print_case("decode plane past 2 GiB", d, end)
+    w = small_attend(144, 1, 4, 4, 1, d, "bf16", [1], [333], L=1, mask_p=2.0)
+    rt = Routes(w)
+    q, ck, cv, rk, rv = w.layer_tensors(0, DEV)
+    mk = rt.max_kv(0)
+    ws = rt.workspace(mk)
+    out, lse = rt.attend(q, ck, cv, rk, rv, 0, workspace=ws, max_kv=mk)
+    rows = end // (2 * d)
+    big_k = torch.empty(1, rows, d, dtype=ck.dtype, device=DEV)
+    big_v = torch.empty_like(big_k)
+    big_k[:, -333:], big_v[:, -333:] = ck, cv
+    cu_ctx, cu_rows = rt.cu_ctx, rt.cu_rows
+    rt.cu_ctx = i32([rows - 333, rows])
+    big, big_lse = rt.attend(q, big_k, big_v, rk, rv, 0, workspace=ws, max_kv=mk)
+    torch.cuda.synchronize()
+    assert torch.equal(out, big) and torch.equal(lse, big_lse)
+    n = rk.shape[1]
+    big_k[:, -n:], big_v[:, -n:] = rk, rv
+    rt.cu_ctx, rt.cu_rows = cu_ctx, cu_rows + (rows - n)
+    big, big_lse = rt.attend(q, ck, cv, big_k, big_v, 0, workspace=ws, max_kv=mk)
     torch.cuda.synchronize()
     assert torch.equal(out, big) and torch.equal(lse, big_lse)
 
