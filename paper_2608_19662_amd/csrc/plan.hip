@@ -75,11 +75,16 @@ __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArg
         const uint64_t mine = i < np2 ? key[i] : 0;
         const int lo32 = (int)(uint32_t)mine, hi32 = (int)(uint32_t)(mine >> 32);
         int pos = 0;
-#pragma unroll 8
-        for (int k = 0; k < 64; ++k) {
+        const int n_keys = min(64, np2 - wave * 64);  // of the run (or none)
+#pragma unroll 4
+        for (int k = 0; k < n_keys; ++k) {
             const uint64_t other = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi32, k) << 32) |
                                    (uint32_t)__builtin_amdgcn_readlane(lo32, k);
             pos += other > mine;
+        }
+        if (n_runs == 1) {  // nothing to merge
+            if (i < n) deal(pos, mine);
+            return;
         }
         if (i < n) key[kPlanThreads + wave * 64 + pos] = mine;  // (padding keys are 0, the smallest)
         __syncthreads();
