@@ -9,6 +9,7 @@
 //     visible (resource, group) routes hold rows, resource-major, each with
 //     the kept rows of its resource.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -134,9 +135,56 @@ __global__ __launch_bounds__(64) void route_walk_kernel(
         const int before = __shfl_up(incl, 1);
         w = lane == 0 ? base : before;
     }
+    // The list [j0, j1) by the whole wave, for the lanes that `mine` says.
+    auto walk = [&](int j0, int j1, bool mine) {
+        for (int js = j0; js < j1; js += kRouteStage) {
+            const int2 staged = stage_resource(js + lane, j1, n_res, req_res, cu_kept);
+            const int n = min(kRouteStage, j1 - js);
+            auto step = [&](auto resources, int k0) {
+                constexpr int U = decltype(resources)::value;
+                uint8_t v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    // lanes of k0 + u < 64 hold ids, or -1 past the list
+                    const int r = __builtin_amdgcn_readlane(staged.x, k0 + u);
+                    v[u] = m[(size_t)max(r, 0) * LG];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int r = __builtin_amdgcn_readlane(staged.x, k0 + u);
+                    if (r >= 0 && mine && v[u]) {
+                        if constexpr (FILL) {
+                            route_res[w++] = r;
+                        } else {
+                            ++cnt;
+                            tok += __builtin_amdgcn_readlane(staged.y, k0 + u);
+                        }
+                    }
+                }
+            };
+            // (a step's instructions count where the list is short)
+            for (int k0 = 0; k0 < n; k0 += 16) {
+                if (n - k0 > 4)
+                    step(std::integral_constant<int, 16>{}, k0);
+                else
+                    step(std::integral_constant<int, 4>{}, k0);
+            }
+        }
+    };
     if constexpr (FLAT) {
+        // (one or two long lists among short ones by the wave, 0.08 us per
+        // resource each, instead of 0.2 by one lane each side by side)
+        const bool is_long = in && j1 - j0 > 32;
+        const int b_before = __shfl_up(b, 1);
+        const bool by_wave = __popcll(__builtin_amdgcn_ballot_w64(is_long && (lane == 0 || b != b_before))) <= 2;
+        for (uint64_t left = by_wave ? __builtin_amdgcn_ballot_w64(is_long) : 0; left;) {
+            const int l = __builtin_ctzll(left), bl = __builtin_amdgcn_readlane(b, l);
+            walk(__builtin_amdgcn_readlane(j0, l), __builtin_amdgcn_readlane(j1, l), in && b == bl);
+            left &= ~__builtin_amdgcn_ballot_w64(b == bl);
+        }
+        const int end = in && !(is_long && by_wave) ? j1 : j0;
 #pragma unroll 4
-        for (int j = j0; j < (in ? j1 : j0); ++j) {
+        for (int j = j0; j < end; ++j) {
             const int r = req_res[j];
             if (r < 0 || r >= n_res || !m[(size_t)r * LG]) continue;
             if constexpr (FILL) {
@@ -146,32 +194,8 @@ __global__ __launch_bounds__(64) void route_walk_kernel(
                 tok += cu_kept[r + 1] - cu_kept[r];
             }
         }
-    }
-    for (int js = j0; !FLAT && js < j1; js += kRouteStage) {
-        const int2 mine = stage_resource(js + lane, j1, n_res, req_res, cu_kept);
-        const int n = min(kRouteStage, j1 - js);
-        constexpr int U = 16;
-        for (int k0 = 0; k0 < n; k0 += U) {
-            uint8_t v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // lanes of k0 + u < 64 hold ids, or -1 past the list
-                const int r = __builtin_amdgcn_readlane(mine.x, k0 + u);
-                v[u] = m[(size_t)max(r, 0) * LG];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int r = __builtin_amdgcn_readlane(mine.x, k0 + u);
-                if (r >= 0 && in && v[u]) {
-                    if constexpr (FILL) {
-                        route_res[w++] = r;
-                    } else {
-                        ++cnt;
-                        tok += __builtin_amdgcn_readlane(mine.y, k0 + u);
-                    }
-                }
-            }
-        }
+    } else {
+        walk(j0, j1, in);
     }
     if constexpr (FILL) {
         if (in && !last) route_off[e + 1] = incl;
@@ -437,12 +461,13 @@ hipError_t launch_build_routes(int n_req, const int32_t* req_res_off, const int3
     z.E = n_req * z.LG;
     z.per_req = (z.LG + 63) / 64;
     const long n = (long)n_req * z.per_req;
-    // A wave for each request costs 1.7 us per thousand of them where its lanes
-    // are mostly idle (few entries per request) and there are more waves than
-    // the CUs hold; lanes that walk lists themselves, 0.4 us per resource.  One
+    // With few entries per request a wave for each leaves most lanes idle and
+    // costs 1.7 us per thousand requests, and some 1 us more to start with than
+    // lanes that walk lists themselves; these cost 0.4 us per resource.  One
     // entry each, 20,000 requests: lists of 2 in 12.6 us instead of 44, of 30 in
-    // 22 instead of 56; 4,097 requests of 64 resources: 39 instead of 26.
-    const bool flat = z.LG <= 16 && n > 4096 && (long)total_req_res * 256 <= n * n_req;
+    // 22 instead of 56; 4,000 of 2: 7.4 instead of 12.4; 64 of 1 / 6 / 8: 5.9 /
+    // 8.2 / 9.2 instead of 7.3 / 8.7 / 8.7; 4,097 of 64: 39 instead of 26.
+    const bool flat = z.LG <= 16 && (long)total_req_res <= std::max(6L, n / 256) * n_req;
     z.n = flat ? (z.E + 63L) / 64 : n;
     auto go = [&](auto count, auto scan, auto fill) {
         hipLaunchKernelGGL(count, dim3((unsigned)z.n), dim3(64), 0, s, z, n_res, req_res_off, req_res, mask, cu_kept,

@@ -21,13 +21,17 @@ pytestmark = pytest.mark.gpu
     # many requests of few entries: lanes of several requests in a wave
     (4097, 30, 1, 1, (0, 12)), (5001, 40, 5, 3, (0, 18)), (8200, 6, 2, 8, (0, 6)), (20001, 9, 1, 3, (0, 3)),
     # and where a wave takes one of them: long lists, as many waves as fit
-    (4097, 70, 1, 2, (30, 70)), (4096, 9, 2, 2, (0, 4)),
+    (4097, 70, 1, 2, (30, 70)), (4096, 9, 2, 2, (0, 4)), (9, 300, 2, 3, (7, 20)),
+    # few entries and short lists, with a long one every so many requests
+    (65, 90, 1, 1, (0, 7)), (64, 90, 1, 1, (1, 4, 20, 33)), (130, 300, 1, 1, (0, 3, 7, 90)),
+    (50, 300, 2, 5, (0, 3, 11, 130)), (700, 90, 1, 3, (0, 2, 50, 64)), (2000, 300, 1, 1, (0, 2, 63, 300)),
 ])
 def test_routes_edges(n_req, pool, L, G, per):
     print("case: route edges", n_req, pool, L, G, per, flush=True)
     rng = np.random.default_rng(n_req + L)
     kept = prefix(rng.integers(1, 50, pool))
-    reqs = [rng.permutation(pool)[:rng.integers(*per)] for _ in range(n_req)]
+    reqs = [rng.permutation(pool)[:rng.integers(*per[:2]) if len(per) == 2 or b % per[2] else per[3]]
+            for b in range(n_req)]
     off, res = prefix([len(r) for r in reqs]), np.concatenate(reqs).astype(np.int32)
     mask = (rng.random((pool, L, G)) < 0.4).astype(np.uint8) * 3  # any non-zero byte is set
     E = n_req * L * G
