@@ -297,11 +297,17 @@ size_t recache_attend_workspace_bytes(int n_req, int max_q, int max_ctx, int max
  *       batch (the same n_req, n_kv_heads and n_q_heads); used by the bf16
  *       kernels (prefill and decode), ignored by fp32.  It only changes
  *       which grid position computes which (request, group): the results
- *       are bit-identical with and without it.  A plan of another batch
+ *       are bit-identical with and without it (a large batch of unequal query
+ *       counts may ignore it).  A plan of another batch
  *       leaves every access in bounds but computes some pairs twice and
  *       others not at all.
  *   workspace: device scratch of recache_attend_workspace_bytes(...) bytes
  *       (may be NULL when that is 0); contents need no initialisation.
+ *
+ * The same call gives the same bits every time.  In bf16 a request's last bits
+ * may differ between batches: the split of its keys over waves and blocks, and
+ * with it the order of the sums, follows from the sizes of the whole call
+ * (prefill: total_q, max_q, max_kv; decode: n_req, max_kv).
  */
 int recache_attend_cached(int dtype, int layer, int n_layers, int n_req, const int32_t* cu_q,
                           const int32_t* cu_ctx, int total_q, int max_q, int max_ctx, int max_kv,
@@ -320,9 +326,10 @@ int recache_attend_cached(int dtype, int layer, int n_layers, int n_req, const i
  * unequal length, and a grid that takes them in request order ends on a
  * tail of long streams (decode) or loads some XCDs more than others
  * (prefill).  For each layer l the pairs p = b * n_kv_heads + g are sorted
- * by their work (longest first; the work counts the 64-key tiles of every
- * query tile of the prefill kernel, plus a fixed cost per tile, from Tq_b,
- * Tc_b and route_tokens), and the sorted pairs are dealt row by row to the
+ * by their work (longest first; the work counts, from Tq_b, Tc_b and
+ * route_tokens, the 64-key tiles that the query rows see in units of
+ * 256 / h rows, h the largest power of two up to 8 that divides the group
+ * size, plus 3 per unit), and the sorted pairs are dealt row by row to the
  * n_kv_heads grid positions, alternating direction.
  *   cu_q/cu_ctx[n_req + 1], route_tokens[n_req][n_layers][n_kv_heads]: as
  *       for recache_attend_cached (route_tokens from recache_build_routes)

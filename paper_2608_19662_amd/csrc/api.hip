@@ -569,7 +569,7 @@ int recache_attend_plan(int n_layers, int n_req, int n_q_heads, int n_kv_heads,
     a.n_req = n_req;
     a.n_layers = n_layers;
     a.n_kv_heads = n_kv_heads;
-    a.wg_rows = attend_block_rows(n_q_heads / n_kv_heads);
+    a.unit_rows = attend_plan_rows(n_q_heads / n_kv_heads);
     a.cu_q = cu_q;
     a.cu_ctx = cu_ctx;
     a.route_tokens = route_tokens;

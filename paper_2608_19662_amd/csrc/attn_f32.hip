@@ -25,10 +25,14 @@
 // + [0, 4) of Q and K (one 16-byte load each), and the keys that the S^T
 // accumulators leave in half h of P.
 //
-// Bound: the fp32 matrix rate (a wave tile is 128 MFMAs of 64 cycles at
+// Bound: one tile after another in a wave, its V's round trip in each, with
+// two blocks per CU to cover it (a wave tile is 128 MFMAs of 64 cycles at
 // head_dim 128; its 32 KB of K and V ask the L2 for 16 B/clk per CU).  The K
-// loads of the next tile are issued behind this tile's S products and the V
-// copies of a tile before them, so both have a product's time to land.
+// loads of the next tile are issued behind this tile's S products.  The V
+// copies of a tile are issued before its S products, but flat copies into LDS
+// make the compiler wait for all of them in front of all but the first of
+// these products; and in the attend form at head_dim 128 16 VGPRs spill, whose
+// reloads wait for the K loads too.
 // Measured at 32 / 8 heads, head_dim 128: six resources of 100 to 500 tokens
 // encode in 140 us (one wave per row and head, a shuffle reduction per key:
 // 965 us), two requests of 150 to 250 queries over them attend in 73 us (669).
@@ -298,8 +302,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args
                     for (int e = 0; e < 4; ++e) top = max(top, w[e] & 0x7fffffffu);
                 }
             }
-            const bool clean = __builtin_amdgcn_ballot_w64(top >= 0x7f800000u) != 0;
-            const uint32_t keep = clean ? 0x7f7fffffu : 0x7fffffffu;  // magnitudes that enter the product
+            const bool unclean = __builtin_amdgcn_ballot_w64(top >= 0x7f800000u) != 0;
+            const uint32_t keep = unclean ? 0x7f7fffffu : 0x7fffffffu;  // magnitudes that enter the product
 #pragma unroll
             for (int r = 0; r < 16; ++r)
 #pragma unroll
@@ -308,7 +312,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(const AttnF32Args
                     oacc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(
                         (__float_as_uint(v) & 0x7fffffffu) <= keep ? v : 0.f, s0[r], oacc[db], 0, 0, 0);
                 }
-            if (__builtin_expect(clean, 0)) {
+            if (__builtin_expect(unclean, 0)) {
                 const int rem0 = min(vis_hi, n_keys - 1) - t * kKeys;
 #pragma unroll 1
                 for (int key = 0; key <= rem0 && key < kKeys; ++key)

@@ -705,8 +705,10 @@ hipError_t launch(const AttnArgs& a, hipStream_t stream) {
 }  // namespace
 
 // The work order's unit of prefill work: 32 * 8 / h rows, h the largest power
-// of two up to 8 that divides the group size.
-int attend_block_rows(int ratio) {
+// of two up to 8 that divides the group size.  A measure of a pair's work, not
+// the rows of a block: those differ between the forms of a launch, and the
+// order has to suit all of them.
+int attend_plan_rows(int ratio) {
     if (ratio < 1) return 0;
     int h = 8;
     while (ratio % h) h >>= 1;

@@ -77,16 +77,6 @@ __device__ __forceinline__ float pair_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-__device__ __forceinline__ float wave_max(float x) {
-    for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
-}
-
-__device__ __forceinline__ float wave_sum(float x) {
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
 // Exclusive prefix sum of `part` over the threads of an NW-wave block, in
 // thread order, and the block total: lane shuffles inside each wave, then
 // the NW wave totals through `wave_tot` (LDS, NW ints).  One barrier; every

@@ -476,11 +476,14 @@ hipError_t launch_dec(const DecodeArgs& a, hipStream_t s) {
     // Context rows past the caches where a layer of them (at most n_req *
     // max_ctx rows) is twice the 256 MB last-level cache or more: they evict
     // what would be found there, of the resources too.  64 requests, 4,096
-    // context rows (1 GB): 283 us a layer instead of 306; 33 requests (528 MB)
-    // over 1,000 / 100 / 32 resources: 135 / 166 / 128 instead of 152 / 184 /
-    // 126.  Below, the part of a context that stays cached is worth more, and
-    // so is the pipeline that this form drains between resources and context:
-    // 250 MB of context 106 us instead of 91, 400 MB 193 instead of 188.
+    // context rows (1 GB): 283 us a layer instead of 306.  Twelve layers in
+    // turn, 4,096 rows per request over 32 / 256 resources, us a layer with the
+    // hint (without): 512 MiB 102 / 114 (107 / 117), 1 GiB 187 / 205 (199 /
+    // 220).  Below, little speaks for either while the layers take turns: 400
+    // MiB 88 / 96 (90 / 98), but 98 (95) with contexts of unequal length; 256
+    // MiB 62 / 69 (61 / 67); 128 MiB 37 / 42 (37 / 41).  Where the next call
+    // reads the same layer, the part that stays cached counts: 256 MiB 60 / 64
+    // (52 / 60).
     const bool nt = (unsigned long)std::min(a.c_rows, a.max_ctx_rows) * a.n_kv_heads * HD * 4 >= (512UL << 20);
     if (big)
         hipLaunchKernelGGL((decode_kernel<HD, true, false>), dim3((unsigned)blocks), dim3(kThreads), 0, s, a);

@@ -338,13 +338,15 @@ struct RouteSearch {
 };
 
 // One block per 256 U / chunks_per_row consecutive rows of the layer's store,
-// whatever routes they belong to, so that every block moves the same bytes in
-// one step, all loads in flight at once.  One thread per row finds its source
-// row: the wave looks up the route of its first row, the 64 routes after it
-// are at hand in the lanes, and only a row past those searches the table.
+// whatever routes they belong to, so that every block moves the same bytes.
+// One thread per row finds its source row: the wave looks up the route of its
+// first row, the 64 routes after it are at hand in the lanes, and only a row
+// past those searches the table.
 // Rows past the routes' total (or past the store) are not written.  NT: loads
 // and stores that leave no trace in the caches, for a layer larger than these
-// hold.  Bound by HBM: one layer of 2,048 resources (1.3 M rows of 256 bytes,
+// hold.  A thread's chunks go one after another (load, wait, store: the bounds
+// test keeps the compiler from loading ahead), with 2,048 threads per CU to
+// cover it.  Bound by HBM: one layer of 2,048 resources (1.3 M rows of 256 bytes,
 // K and V, out of 9.2 GB) in 242 us, 5.7 TB/s.  Without NT 268, with 8 chunks
 // per thread instead of 4 252 (both with each thread looking its rows up);
 // with a block per route in steps of eight chunks per thread 286.
@@ -437,9 +439,13 @@ hipError_t launch_store_routes(int elem_bytes, int layer, int n_res, const int32
     const long rows = 256 * U / cpr;  // per block
     const long blocks = (store_rows + rows - 1) / rows;
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    // K and V read and written: above the last-level cache's 256 MB nothing
-    // of it would be found there by the next reader; a smaller store is left
-    // in reach of the attention that follows
+    // Past the caches where K and V, read and written, take more than the 256
+    // MB of the last-level cache.  The store alone is faster so at every size
+    // (24 / 91 / 185 / 473 MiB of stored rows: 12.4 / 39 / 75 / 174 us instead
+    // of 13.6 / 42 / 81 / 188), and with it a program that fills all layers
+    // before it attends.  Where the layer's attention follows at once, a
+    // cached store is found by it: both together, for 91 / 185 / 275 / 473 MiB,
+    // 87 / 126 / 165 / 245 us through the caches, 92 / 131 / 167 / 236 past them.
     const bool nt = 4 * store_rows * cpr * 16 > (256L << 20);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, cpr, n_kv_heads, (int)n_routes,

@@ -55,8 +55,8 @@ hipError_t launch_attn_mfma(const AttnArgs& a, bool encode, int head_dim, hipStr
 // Prefill of small grids: 32 (row, head) columns per block, keys split over
 // its waves (4 or 8); fills n_qt with the column blocks per unit.
 hipError_t launch_attn_split(const AttnArgs& a, int head_dim, int waves, hipStream_t stream);
-// Query rows of one prefill block (32 per row block) for a group size.
-int attend_block_rows(int ratio);
+// The work order's unit of prefill work, in query rows, for a group size.
+int attend_plan_rows(int ratio);
 
 // fp32 reference-precision attention (encode or conversation attend).
 struct AttnF32Args {
@@ -167,10 +167,10 @@ size_t decode_workspace_bytes(long parts, int n_q_heads, int head_dim);
 // b * n_kv_heads + g sorted by their work, longest first, dealt in snake order
 // over the n_kv_heads grid positions.
 constexpr int kMaxPlanPairs = 8192;  // n_req * n_kv_heads per plan (sorted in LDS)
-constexpr int kPlanBlockCost = 3;    // fixed cost of a block, in 64-key tiles
+constexpr int kPlanUnitCost = 3;     // fixed cost of a unit of work, in 64-key tiles
 struct PlanArgs {
     int n_req, n_layers, n_kv_heads;
-    int wg_rows;  // query rows per prefill block (attend_block_rows)
+    int unit_rows;  // query rows per unit of work (attend_plan_rows)
     const int32_t* cu_q;
     const int32_t* cu_ctx;
     const int32_t* route_tokens;  // [n_req][n_layers][n_kv_heads]

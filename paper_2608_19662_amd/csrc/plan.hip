@@ -41,15 +41,16 @@ __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArg
             const int q_len = a.cu_q[b + 1] - a.cu_q[b];
             const int tc = a.cu_ctx[b + 1] - a.cu_ctx[b];
             const int s_vis = a.route_tokens[((size_t)b * a.n_layers + layer) * G + g];
-            // Cost in 64-key tiles: the query tiles of wg_rows rows each see
+            // Cost in 64-key tiles: units of unit_rows query rows each see
             // the keys up to their last row (stream positions <= off + row),
-            // plus a fixed cost per block.
+            // plus a fixed cost per unit.  (The units are a measure only: the
+            // forms of a prefill launch cut the rows in other ways.)
             long work = 0;
             if (q_len > 0) {
                 const long off = (long)s_vis + tc - q_len;
-                for (long r0 = 0; r0 < q_len; r0 += a.wg_rows) {
-                    const long last = min(r0 + a.wg_rows, (long)q_len) - 1;
-                    work += max(off + last, 0L) / 64 + 1 + kPlanBlockCost;
+                for (long r0 = 0; r0 < q_len; r0 += a.unit_rows) {
+                    const long last = min(r0 + a.unit_rows, (long)q_len) - 1;
+                    work += max(off + last, 0L) / 64 + 1 + kPlanUnitCost;
                 }
             }
             if (work > 0x7fffffffL) work = 0x7fffffffL;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArg
 }  // namespace
 
 hipError_t launch_attend_plan(const PlanArgs& a, hipStream_t stream) {
-    if (a.n_req < 1 || a.n_kv_heads < 1 || a.n_layers < 1 || a.wg_rows < 1 ||
+    if (a.n_req < 1 || a.n_kv_heads < 1 || a.n_layers < 1 || a.unit_rows < 1 ||
         (long)a.n_req * a.n_kv_heads > kMaxPlanPairs)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(attend_plan_kernel, dim3((unsigned)a.n_layers), dim3(kPlanThreads), 0, stream, a);

@@ -143,8 +143,8 @@ def plan_reference(cu_q, cu_ctx, route_tokens, n_layers, n_q_heads, n_kv_heads):
     """The work order the plan builder documents, in plain Python: per layer
     the pairs b * G + g sorted by (work descending, pair ascending), the
     k-th sorted pair at grid row k // G, position k % G (even rows) or
-    G - 1 - k % G (odd rows).  Work: for every prefill query tile of wg
-    rows, its 64-key tiles (keys up to its last row) plus 3."""
+    G - 1 - k % G (odd rows).  Work: for every unit of wg query rows, its
+    64-key tiles (keys up to its last row) plus 3."""
     G = n_kv_heads
     ratio = n_q_heads // G
     h = 8

@@ -40,8 +40,8 @@ def test_encode_resource_longer_than_max_len(dtype):
     cu = w.cu_len
     # rows of the long resource past what a grid sized by max_len = 200 covers
     # are NaN in every head; the short resources are computed normally
-    # (fp32: one wave per row up to max_len; bf16 with 4 query heads per KV
-    # head: 32-row tiles, ceil(200 / 32) = 7 of them)
+    # (fp32: rows up to max_len; bf16: 32-row blocks, ceil(200 / 32) = 7 of
+    # them)
     covered = 200 if dtype == "f32" else 224
     assert torch.isnan(out[cu[1] + covered:cu[2]].float()).all()
     assert torch.isnan(lse[:, cu[1] + covered:cu[2]]).all()
@@ -57,7 +57,8 @@ def test_prefill_queries_past_max_q():
     q, ck, cv, rk, rv = w.layer_tensors(0, DEV)
     out, lse = rt.attend(q, ck, cv, rk, rv, 0)
     torch.cuda.synchronize()
-    # the grid covers ceil(170 / 32) = 6 tiles of 32 rows per request
+    # (a split over keys computes rows up to max_q; the forms in blocks of rows,
+    # up to 192, are in test_gpu_prefill_forms.py)
     assert torch.isnan(out[192:300].float()).all() and torch.isnan(lse[:, 192:300]).all()
     assert torch.isfinite(out[300:340].float()).all()
 
