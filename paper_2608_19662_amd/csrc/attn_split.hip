@@ -315,6 +315,9 @@ __global__ __launch_bounds__(W * 64, 2) void attn_split_kernel(const AttnArgs a)
     if (wave < n_tiles) {
         set_tile(wave);
         copy(false, kb);
+        // (the first wait counts on this order, which two arrays alone leave open)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
         copy(true, vb);
     }
     // (the loop ends from its middle, so that on its back edge a V copy always
