@@ -300,42 +300,22 @@ __global__ __launch_bounds__(1024) void store_offsets_kernel(
     if (tid == 0) off[n] = carry;
 }
 
-// The search of a wave's 64 lanes together for the last route that starts at
-// or before a row (off non-decreasing, off[0] <= row): two or three round trips
-// for a table that a binary search crosses in fourteen.  The loads of the
-// first step depend on nothing (start), and those of the last leave the starts
-// of the routes after the one found in the lanes as well.
-struct RouteSearch {
-    int lo = 0, n;  // the route is one of [lo, lo + n)
-    int w0, w1;     // lane k: starts of route lo + k * step, and of route lo + 64 + k
-
-    __device__ __forceinline__ int step() const { return (n + 63) / 64; }
-    __device__ __forceinline__ void load(const int32_t* off, int n_routes) {
-        const int lane = threadIdx.x & 63;
-        w0 = off[min(lo + lane * step(), n_routes)];
-        w1 = off[min(lo + 64 + lane, n_routes)];
+// Last index i in [lo, hi] with off[i] <= row (off non-decreasing, off[lo] <=
+// row), by the 64 lanes of a wave together: two or three round trips for a
+// table that a binary search crosses in fourteen.
+__device__ __forceinline__ int wave_find_route(const int32_t* off, int lo, int hi, long row) {
+    const int lane = threadIdx.x & 63;
+    int n = hi - lo + 1;
+    while (n > 1) {
+        const int step = (n + 63) / 64;
+        const bool le = lane * step < n && off[lo + lane * step] <= row;
+        const int c = max(1, (int)__popcll(__builtin_amdgcn_ballot_w64(le)));
+        const int skip = (c - 1) * step;
+        n = min(step, n - skip);
+        lo += skip;
     }
-    __device__ __forceinline__ void start(const int32_t* off, int n_routes) {
-        n = n_routes;
-        load(off, n_routes);
-    }
-    // The route, and in `next` lane k the start of the k-th one after it.
-    __device__ __forceinline__ int find(const int32_t* off, int n_routes, long row, int* next) {
-        const int lane = threadIdx.x & 63;
-        for (;;) {
-            const int s = step();
-            const int c = max(1, (int)__popcll(__builtin_amdgcn_ballot_w64(lane * s < n && w0 <= row)));
-            if (s == 1) {
-                const int near = __shfl(w0, min(c + lane, 63)), far = __shfl(w1, max(c + lane - 64, 0));
-                *next = c + lane < 64 ? near : far;
-                return lo + c - 1;
-            }
-            lo += (c - 1) * s;
-            n = min(s, n - (c - 1) * s);
-            load(off, n_routes);
-        }
-    }
-};
+    return lo;
+}
 
 // One block per 256 U / chunks_per_row consecutive rows of the layer's store,
 // whatever routes they belong to, so that every block moves the same bytes.
@@ -360,15 +340,14 @@ __global__ __launch_bounds__(256) void store_routes_kernel(
     __shared__ long src_row[32 * U];  // (8 chunks per row or more)
     const int sh = __builtin_ctz(chunks_per_row);  // a power of two
     const long first = (long)blockIdx.x * (256 * U >> sh);
-    RouteSearch search;
-    search.start(off, n_routes);
     const long end = min(first + (256 * U >> sh), min(store_rows, (long)off[n_routes]));
     if (end <= first) return;
     const int n_rows = (int)(end - first);
     if ((int)(threadIdx.x & ~63u) < n_rows) {
         const long row = min(first + (long)threadIdx.x, end - 1);
-        int next;  // where the routes after i0 start
-        const int i0 = search.find(off, n_routes, first + (threadIdx.x & ~63u), &next);
+        const int i0 = wave_find_route(off, 0, n_routes - 1, first + (threadIdx.x & ~63u));
+        const int lane = threadIdx.x & 63;
+        const int next = off[min(i0 + 1 + lane, n_routes)];  // where the routes after i0 start
         int lo = 0;  // routes after i0 that start at or before the row (all lanes take every step)
 #pragma unroll
         for (int step = 32; step >= 1; step >>= 1)
