@@ -76,12 +76,17 @@ __global__ __launch_bounds__(kPlanThreads) void attend_plan_kernel(const PlanArg
         const uint64_t mine = i < np2 ? key[i] : 0;
         const int lo32 = (int)(uint32_t)mine, hi32 = (int)(uint32_t)(mine >> 32);
         int pos = 0;
-        const int n_keys = min(64, np2 - wave * 64);  // of the run (or none)
-#pragma unroll 4
-        for (int k = 0; k < n_keys; ++k) {
+        auto rank = [&](int k) {
             const uint64_t other = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi32, k) << 32) |
                                    (uint32_t)__builtin_amdgcn_readlane(lo32, k);
             pos += other > mine;
+        };
+        if (np2 < 64) {
+#pragma unroll 4
+            for (int k = 0; k < np2; ++k) rank(k);
+        } else {
+#pragma unroll 8
+            for (int k = 0; k < 64; ++k) rank(k);
         }
         if (n_runs == 1) {  // nothing to merge
             if (i < n) deal(pos, mine);

@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n_res,G,p,lens", [
     (1, 1, 1.0, (1, 2)), (1, 8, 1.0, (63, 66)), (700, 8, 0.01, (1, 4)), (300, 3, 0.5, (1, 200)),
     (90, 8, 1.0, (64, 65)),
+    # tables around one and two steps of a wave's search
+    (8, 8, 0.7, (1, 40)), (13, 5, 1.0, (1, 3)), (512, 8, 0.3, (1, 30)), (683, 6, 0.3, (1, 30)),
 ])
 def test_store_routes_edges(dtype, d, n_res, G, p, lens):
     print("case: store edges", dtype, d, n_res, G, p, lens, flush=True)
