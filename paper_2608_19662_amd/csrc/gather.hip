@@ -9,7 +9,6 @@
 //     visible (resource, group) routes hold rows, resource-major, each with
 //     the kept rows of its resource.
 #include <algorithm>
-#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -94,6 +93,33 @@ __device__ __forceinline__ size_t slice_last(const Slices& z, uint32_t sl) {
     return (size_t)(sl / (uint32_t)z.per_req) * z.LG + min((int)(sl % (uint32_t)z.per_req) * 64 + 64, z.LG);
 }
 
+// Resources k0 .. k0 + 15 of a staged list for the entries of the lanes that
+// are `in`: mask bytes first, then the counts or, with FILL, the ids.
+template <bool FILL>
+__device__ __forceinline__ void walk_step(const int2 mine, const int k0, const bool in, const uint8_t* m, const int LG,
+                                          int& cnt, int& tok, int& w, int32_t* __restrict__ route_res) {
+    constexpr int U = 16;
+    uint8_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        // lanes of k0 + u < 64 hold ids, or -1 past the list
+        const int r = __builtin_amdgcn_readlane(mine.x, k0 + u);
+        v[u] = m[(size_t)max(r, 0) * LG];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int r = __builtin_amdgcn_readlane(mine.x, k0 + u);
+        if (r >= 0 && in && v[u]) {
+            if constexpr (FILL) {
+                route_res[w++] = r;
+            } else {
+                ++cnt;
+                tok += __builtin_amdgcn_readlane(mine.y, k0 + u);
+            }
+        }
+    }
+}
+
 // Entry e = (b * L + l) * G + g, one wave per slice of 64 entries of a request.
 // First pass: count the visible resources and their kept rows; route_off[e + 1]
 // gets the counts' inclusive scan within the slice.  route_scan_kernel makes
@@ -135,42 +161,6 @@ __global__ __launch_bounds__(64) void route_walk_kernel(
         const int before = __shfl_up(incl, 1);
         w = lane == 0 ? base : before;
     }
-    // The list [j0, j1) by the whole wave, for the lanes that `mine` says.
-    auto walk = [&](int j0, int j1, bool mine) {
-        for (int js = j0; js < j1; js += kRouteStage) {
-            const int2 staged = stage_resource(js + lane, j1, n_res, req_res, cu_kept);
-            const int n = min(kRouteStage, j1 - js);
-            auto step = [&](auto resources, int k0) {
-                constexpr int U = decltype(resources)::value;
-                uint8_t v[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    // lanes of k0 + u < 64 hold ids, or -1 past the list
-                    const int r = __builtin_amdgcn_readlane(staged.x, k0 + u);
-                    v[u] = m[(size_t)max(r, 0) * LG];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int r = __builtin_amdgcn_readlane(staged.x, k0 + u);
-                    if (r >= 0 && mine && v[u]) {
-                        if constexpr (FILL) {
-                            route_res[w++] = r;
-                        } else {
-                            ++cnt;
-                            tok += __builtin_amdgcn_readlane(staged.y, k0 + u);
-                        }
-                    }
-                }
-            };
-            // (a step's instructions count where the list is short)
-            for (int k0 = 0; k0 < n; k0 += 16) {
-                if (n - k0 > 4)
-                    step(std::integral_constant<int, 16>{}, k0);
-                else
-                    step(std::integral_constant<int, 4>{}, k0);
-            }
-        }
-    };
     if constexpr (FLAT) {
         // (one or two long lists among short ones by the wave, 0.08 us per
         // resource each, instead of 0.2 by one lane each side by side)
@@ -178,9 +168,15 @@ __global__ __launch_bounds__(64) void route_walk_kernel(
         const int b_before = __shfl_up(b, 1);
         const bool by_wave = __popcll(__builtin_amdgcn_ballot_w64(is_long && (lane == 0 || b != b_before))) <= 2;
         for (uint64_t left = by_wave ? __builtin_amdgcn_ballot_w64(is_long) : 0; left;) {
-            const int l = __builtin_ctzll(left), bl = __builtin_amdgcn_readlane(b, l);
-            walk(__builtin_amdgcn_readlane(j0, l), __builtin_amdgcn_readlane(j1, l), in && b == bl);
-            left &= ~__builtin_amdgcn_ballot_w64(b == bl);
+            const int l = __builtin_ctzll(left);
+            const bool its = in && b == __builtin_amdgcn_readlane(b, l);
+            const int end = __builtin_amdgcn_readlane(j1, l);
+            for (int js = __builtin_amdgcn_readlane(j0, l); js < end; js += kRouteStage) {
+                const int2 mine = stage_resource(js + lane, end, n_res, req_res, cu_kept);
+                for (int k0 = 0; k0 < min(kRouteStage, end - js); k0 += 16)
+                    walk_step<FILL>(mine, k0, its, m, LG, cnt, tok, w, route_res);
+            }
+            left &= ~__builtin_amdgcn_ballot_w64(its);
         }
         const int end = in && !(is_long && by_wave) ? j1 : j0;
 #pragma unroll 4
@@ -194,8 +190,11 @@ __global__ __launch_bounds__(64) void route_walk_kernel(
                 tok += cu_kept[r + 1] - cu_kept[r];
             }
         }
-    } else {
-        walk(j0, j1, in);
+    }
+    for (int js = j0; !FLAT && js < j1; js += kRouteStage) {
+        const int2 mine = stage_resource(js + lane, j1, n_res, req_res, cu_kept);
+        const int n = min(kRouteStage, j1 - js);
+        for (int k0 = 0; k0 < n; k0 += 16) walk_step<FILL>(mine, k0, in, m, LG, cnt, tok, w, route_res);
     }
     if constexpr (FILL) {
         if (in && !last) route_off[e + 1] = incl;
@@ -473,7 +472,9 @@ hipError_t launch_build_routes(int n_req, const int32_t* req_res_off, const int3
     // entry each, 20,000 requests: lists of 2 in 12.6 us instead of 44, of 30 in
     // 22 instead of 56; 4,000 of 2: 7.4 instead of 12.4; 64 of 1 / 6 / 8: 5.9 /
     // 8.2 / 9.2 instead of 7.3 / 8.7 / 8.7; 4,097 of 64: 39 instead of 26.
-    const bool flat = z.LG <= 16 && (long)total_req_res <= std::max(6L, n / 256) * n_req;
+    // With more entries only the shortest lists gain: 288 entries, 8 requests of
+    // 1 / 2 resources 6.7 / 7.3 instead of 8.6 each, of 4 8.3 instead of 8.6.
+    const bool flat = (long)total_req_res <= (z.LG <= 16 ? std::max(6L, n / 256) : 2L) * n_req;
     z.n = flat ? (z.E + 63L) / 64 : n;
     auto go = [&](auto count, auto scan, auto fill) {
         hipLaunchKernelGGL(count, dim3((unsigned)z.n), dim3(64), 0, s, z, n_res, req_res_off, req_res, mask, cu_kept,
