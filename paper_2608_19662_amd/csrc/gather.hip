@@ -472,9 +472,9 @@ hipError_t launch_build_routes(int n_req, const int32_t* req_res_off, const int3
     // entry each, 20,000 requests: lists of 2 in 12.6 us instead of 44, of 30 in
     // 22 instead of 56; 4,000 of 2: 7.4 instead of 12.4; 64 of 1 / 6 / 8: 5.9 /
     // 8.2 / 9.2 instead of 7.3 / 8.7 / 8.7; 4,097 of 64: 39 instead of 26.
-    // With more entries only the shortest lists gain: 288 entries, 8 requests of
-    // 1 / 2 resources 6.7 / 7.3 instead of 8.6 each, of 4 8.3 instead of 8.6.
-    const bool flat = (long)total_req_res <= (z.LG <= 16 ? std::max(6L, n / 256) : 2L) * n_req;
+    // With more entries the line lies at 4: 288 entries, 8 requests of 1 / 2 / 4 /
+    // 5 resources 6.7 / 7.3 / 8.3 / 8.9 instead of 8.6, 8.6, 8.6 and 8.8.
+    const bool flat = (long)total_req_res <= (z.LG <= 16 ? std::max(6L, n / 256) : 4L) * n_req;
     z.n = flat ? (z.E + 63L) / 64 : n;
     auto go = [&](auto count, auto scan, auto fill) {
         hipLaunchKernelGGL(count, dim3((unsigned)z.n), dim3(64), 0, s, z, n_res, req_res_off, req_res, mask, cu_kept,

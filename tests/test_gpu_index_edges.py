@@ -25,6 +25,7 @@ pytestmark = pytest.mark.gpu
     # few entries and short lists, with a long one every so many requests
     (65, 90, 1, 1, (0, 7)), (64, 90, 1, 1, (1, 4, 20, 33)), (130, 300, 1, 1, (0, 3, 7, 90)),
     (50, 300, 2, 5, (0, 3, 11, 130)), (700, 90, 1, 3, (0, 2, 50, 64)), (2000, 300, 1, 1, (0, 2, 63, 300)),
+    (7, 30, 36, 8, (0, 5)), (60, 90, 13, 5, (0, 3, 30, 80)),
 ])
 def test_routes_edges(n_req, pool, L, G, per):
     print("case: route edges", n_req, pool, L, G, per, flush=True)
